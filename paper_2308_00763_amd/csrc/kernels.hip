@@ -857,7 +857,7 @@ __device__ __forceinline__ void pass_a_tile(const StepArgs& a, int tile, PassALd
         m = block_max<kWavesA>(m, lds.red_d[0]);
         tile_m = m;
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) wt[i] = valid[i] ? exp(L[i] - m) : 0.0;
+        for (int i = 0; i < PPT; ++i) wt[i] = valid[i] ? exp_nonpos(L[i] - m) : 0.0;
     } else {
         int sm = INT32_MIN;
 #pragma unroll

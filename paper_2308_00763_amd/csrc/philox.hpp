@@ -57,18 +57,141 @@ __device__ __forceinline__ double uniform53(uint32_t hi, uint32_t lo)
     return (double)bits * 0x1.0p-53;
 }
 
+// The same value times 2^32, exact (53 bits): two conversions of 32 bits and
+// one fused multiply-add.
+__device__ __forceinline__ double uniform53_times_2_32(uint32_t hi, uint32_t lo)
+{
+    return __builtin_fma((double)(lo >> 11), 0x1.0p-21, (double)hi);
+}
+
+// The three functions of the double Box-Muller, for its own arguments only.
+// The library's log, sqrt and sincos take any argument; as inlined they were
+// 98, 22 and 157 vector instructions a particle and most of the double pass A,
+// which is bound by vector issue (87 % busy at 2^23 particles).  These are about
+// 30, 11 and 36, and pass A needs 62 registers instead of 92 (8 waves per
+// SIMD, not 5): a step of 2^23 + 1 particles (r = 8) 182 -> 161 us, of 2^20
+// 31.8 -> 29.6 us.  Largest error of a normal over 2^21 draws 1.5e-15 (the
+// library's 4.2e-15: it rounds 2 pi u before it reduces it).
+// Polynomial coefficients: the functions' own Taylor series economised at
+// Chebyshev nodes in 60 digits; what they leave out is below 2e-17 of the
+// result.
+
+// A constant in scalar registers, formed where it is used: left to itself the
+// compiler keeps a loop's double constants in vector registers (40 of them).
+__device__ __forceinline__ double coef(double c)
+{
+    __asm__ volatile("" : "+s"(c));
+    return c;
+}
+
+// exp(d) for d <= 0, the weights: d = k ln 2 + r, |r| <= ln 2 / 2, exp(r) = 1 + r
+// + r^2 P(r) (21 instructions against the library's 42).
+__device__ __forceinline__ double exp_nonpos(double d)
+{
+    d = d < -800.0 ? -800.0 : d;  // rounds to 0 from there on; a NaN stays
+    const double k = __builtin_rint(d * coef(0x1.71547652b82fep+0));
+    const double r = __builtin_fma(k, -coef(0x1.a39ef35793c76p-33), __builtin_fma(k, -coef(0x1.62e42feep-1), d));
+    double p = coef(0x1.af38a0d2d9620p-26);
+    p = __builtin_fma(p, r, coef(0x1.28917e2c43a66p-22));
+    p = __builtin_fma(p, r, coef(0x1.71de0db21e27fp-19));
+    p = __builtin_fma(p, r, coef(0x1.a019b9133a48ap-16));
+    p = __builtin_fma(p, r, coef(0x1.a01a01a7c327ap-13));
+    p = __builtin_fma(p, r, coef(0x1.6c16c1788a49bp-10));
+    p = __builtin_fma(p, r, coef(0x1.11111111109b4p-7));
+    p = __builtin_fma(p, r, coef(0x1.5555555553d67p-5));
+    p = __builtin_fma(p, r, coef(0x1.5555555555556p-3));
+    p = __builtin_fma(p, r, 0.5);
+    return __builtin_ldexp(1.0 + __builtin_fma(r * r, p, r), (int)k);
+}
+
+// -2 ln(a) for a in [2^-53, 1].  a = 2^e m with m in [sqrt(1/2), sqrt(2)), f =
+// m - 1, s = f / (2 + f): ln m = 2 atanh(s) = f - h + s (h + R) with h = f^2 / 2
+// and R the series past 2 s, over s.
+__device__ __forceinline__ double minus_2_ln(double a)
+{
+    const uint32_t hx = (uint32_t)__double2hiint(a);
+    const int e = (int)(hx - 0x3fe6a09fu) >> 20;  // <= 0: floor
+    const double m = __hiloint2double((int)(hx - ((uint32_t)e << 20)), __double2loint(a));
+    const double f = m - 1.0;
+    const double d = f + 2.0;
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    double s = f * y;
+    s = __builtin_fma(__builtin_fma(-d, s, f), y, s);
+    const double z = s * s;
+    double p = coef(0x1.2b584dae87b55p-3);
+    p = __builtin_fma(p, z, coef(0x1.39fe60271f67fp-3));
+    p = __builtin_fma(p, z, coef(0x1.7462b4ad0d879p-3));
+    p = __builtin_fma(p, z, coef(0x1.c71c62e579789p-3));
+    p = __builtin_fma(p, z, coef(0x1.2492492df14dfp-2));
+    p = __builtin_fma(p, z, coef(0x1.99999999952e2p-2));
+    p = __builtin_fma(p, z, coef(0x1.5555555555558p-1));
+    const double h = 0.5 * f * f;
+    const double ed = (double)e;
+    // e ln 2 in two parts, the first exact (ln 2's leading 32 bits)
+    const double t = __builtin_fma(s, __builtin_fma(z, p, h), ed * coef(0x1.a39ef35793c76p-33));
+    const double l = __builtin_fma(ed, coef(0x1.62e42feep-1), -((h - t) - f));
+    return -2.0 * l;
+}
+
+// sqrt(x) for x = 0 or x in [2^-53, 128]: reciprocal square root and three
+// Goldschmidt corrections (no scaling: the argument is far from the range's
+// ends; zero becomes 1e-150, which moves no position).
+__device__ __forceinline__ double sqrt_near(double x)
+{
+    x = __builtin_fmax(x, 1e-300);
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return g;
+}
+
+// cos and sin of 2 pi u 2^-32 for u in [0, 2^32): the quadrant and the rest of
+// u are exact, so the angle is reduced before it is rounded.
+__device__ __forceinline__ void cos_sin_turn(double u, double& c, double& s)
+{
+    const double k = __builtin_rint(u * 0x1.0p-30);  // quarter turns
+    const double t = __builtin_fma(k, -0x1.0p30, u) * coef(0x1.921fb54442d18p+2 * 0x1.0p-32);
+    const int q = (int)k;
+    const double z = t * t;
+    double p = coef(0x1.5e0b19f699a14p-33);
+    p = __builtin_fma(p, z, coef(-0x1.ae600b02b0573p-26));
+    p = __builtin_fma(p, z, coef(0x1.71de37968a0a7p-19));
+    p = __builtin_fma(p, z, coef(-0x1.a01a019e83aaep-13));
+    p = __builtin_fma(p, z, coef(0x1.1111111110bb2p-7));
+    p = __builtin_fma(p, z, coef(-0x1.5555555555555p-3));
+    const double sn = __builtin_fma(t * z, p, t);
+    double w = coef(-0x1.907da3658b573p-37);
+    w = __builtin_fma(w, z, coef(0x1.1eeb68e9387c9p-29));
+    w = __builtin_fma(w, z, coef(-0x1.27e4fa17da071p-22));
+    w = __builtin_fma(w, z, coef(0x1.a01a019f4eb01p-16));
+    w = __builtin_fma(w, z, coef(-0x1.6c16c16c16967p-10));
+    w = __builtin_fma(w, z, coef(0x1.5555555555555p-5));
+    const double hz = 0.5 * z, one = 1.0 - hz;
+    const double cs = one + __builtin_fma(z * z, w, (1.0 - one) - hz);
+    const bool swap = (q & 1) != 0;
+    const double a = swap ? sn : cs, b = swap ? cs : sn;
+    // signs: cos is negative in quadrants 1 and 2, sin in 2 and 3
+    const int sc = ((q + 1) & 2) << 30, ss = (q & 2) << 30;
+    c = __hiloint2double(__double2hiint(a) ^ sc, __double2loint(a));
+    s = __hiloint2double(__double2hiint(b) ^ ss, __double2loint(b));
+}
+
 // Box-Muller in double (Box & Muller 1958): rho = sqrt(-2 ln(1 - u_a)),
 // (z_x, z_y) = rho (cos 2 pi u_b, sin 2 pi u_b).  Written operation by
 // operation; the library is compiled without contraction so each product
 // and sum rounds separately.
 __device__ __forceinline__ void normal_pair_f64(const u32x4& w, double& zx, double& zy)
 {
-    const double ua = uniform53(w.v0, w.v1);
-    const double ub = uniform53(w.v2, w.v3);
-    const double rho = sqrt(-2.0 * log(1.0 - ua));
-    const double ang = 6.283185307179586 * ub;
+    // 1 - u_a is a multiple of 2^-53 in (0, 1]: exact
+    const double rho = sqrt_near(minus_2_ln(__builtin_fma(uniform53_times_2_32(w.v0, w.v1), -0x1.0p-32, 1.0)));
     double s, c;
-    sincos(ang, &s, &c);
+    cos_sin_turn(uniform53_times_2_32(w.v2, w.v3), c, s);
     zx = rho * c;
     zy = rho * s;
 }
