@@ -1154,7 +1154,7 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
             en.fid = k;
             en.tile_base = tiles;
             en.t = h->t + 1;
-            en.pad = 0;
+            en.tiles = h->L.ntiles;
             if (!same)
                 for (int i = 0; i < h->L.ntiles; ++i) tmap[tiles + i] = ne;
             tiles += h->L.ntiles;

@@ -55,6 +55,19 @@ __device__ __forceinline__ gbl_t<T>* gbl(T* p)
     return (gbl_t<T>*)p;
 }
 
+// The batch's plan (filter arguments, entries, tile map) does not change while
+// a kernel runs, so the kernels read it through the constant address space:
+// its uniform reads become scalar loads, which wait on their own counter (a
+// tile's arguments can arrive while vector loads of its inputs are in flight)
+// and come through the scalar cache.
+template <typename T>
+using cst_t = __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ const cst_t<T>* cst(const T* p)
+{
+    return (const cst_t<T>*)p;
+}
+
 // The bulk outputs that the next kernel reads (pass A's propagated positions
 // and tile prefix sums, pass C's resampled state) of a single filter that is
 // not FP64 and has at most kWtMaxTiles tiles (StepArgs::wt) are stored at
@@ -166,24 +179,54 @@ __device__ __forceinline__ int disk_half_width(int r, int dy)
     return h;
 }
 
-// Pixel sum over the disk; `p` points at the table entry of the disk's
-// top-left corner (row cy - (r - 1), column cx - (r - 1)).
-template <int RC>
-__device__ __forceinline__ int disk_sum_prefix(const uint16_t* p, int r)
+// Half widths of the disk's rows, in LDS (`hw`, entry i for dy = i - (r - 1));
+// the caller synchronises before they are read.
+__device__ __forceinline__ void fill_half_widths(uint8_t* hw, int r)
 {
-    int s = 0;
+    for (int i = threadIdx.x; i < 2 * r - 1; i += blockDim.x) hw[i] = (uint8_t)disk_half_width(r, i - (r - 1));
+}
+
+// Pixel sums over the disk at M positions of the row-prefix table; off[j] is the entry of the disk's top-left corner (row cy -
+// (r - 1), column cx - (r - 1)).  Row by row, so that a row's half width is
+// read once for all positions (four at a time, `hw` is 4-byte aligned).  The
+// half width had been a square root per row and particle: 3 10^6 BF16
+// particles, r = 12, pass A 62 -> 30 us.
+template <int M>
+__device__ __forceinline__ void disk_sums_rows(const uint16_t* pref, const int (&off)[M], int (&s)[M], int r,
+                                               const uint8_t* hw)
+{
+#pragma unroll
+    for (int j = 0; j < M; ++j) s[j] = 0;
+    const uint16_t* base = pref + kPrefBase + (r - 1);
+    uint32_t h4 = 0;
+#pragma unroll 1
+    for (int i = 0; i < 2 * r - 1; ++i, base += kPrefPitch) {
+        if ((i & 3) == 0) h4 = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t*>(hw + i));
+        const int h = (int)(h4 & 0xFF);
+        h4 >>= 8;
+        const uint16_t *plus = base + h + 1, *minus = base - h;
+#pragma unroll
+        for (int j = 0; j < M; ++j) s[j] += (int)plus[off[j]] - (int)minus[off[j]];
+    }
+}
+
+// The same with the rows unrolled for a compile-time radius.
+template <int RC, int M>
+__device__ __forceinline__ void disk_sums_prefix(const uint16_t* pref, const int (&off)[M], int (&s)[M], int r,
+                                                 const uint8_t* hw)
+{
     if constexpr (RC > 0) {
         constexpr DiskRows<RC> rows{};
 #pragma unroll
-        for (int i = 0; i < DiskRows<RC>::ROWS; ++i) s += (int)p[rows.plus[i]] - (int)p[rows.minus[i]];
-    } else {
-        for (int i = 0; i < 2 * r - 1; ++i) {
-            const int h = disk_half_width(r, i - (r - 1));
-            const uint16_t* row = p + i * kPrefPitch + kPrefBase + (r - 1);
-            s += (int)row[h + 1] - (int)row[-h];
+        for (int j = 0; j < M; ++j) {
+            const uint16_t* p = pref + off[j];
+            s[j] = 0;
+#pragma unroll
+            for (int i = 0; i < DiskRows<RC>::ROWS; ++i) s[j] += (int)p[rows.plus[i]] - (int)p[rows.minus[i]];
         }
+    } else {
+        disk_sums_rows<M>(pref, off, s, r, hw);
     }
-    return s;
 }
 
 // The same sum read straight from the frame with edge clamping (used when a
@@ -221,6 +264,17 @@ __device__ __forceinline__ int offset_cell(float v, int origin, int lo, int hi)
     v = __builtin_amdgcn_fmed3f(v, (float)(lo - origin), (float)(hi - origin));
     const float fl = floorf(v);
     return origin + (int)fl + ((v - fl) >= 0.5f ? 1 : 0);
+}
+
+// The pixel cell of a float position counted from the origin cell, half-up:
+// the instruction rounds floor(v + 1/2) exactly (compared with offset_cell
+// for every float up to 2^22) and saturates, so the callers clamp or compare
+// the integer.
+__device__ __forceinline__ int round_half_up(float v)
+{
+    int r;
+    __asm__("v_cvt_rpi_i32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
 }
 
 template <int DT>
@@ -357,8 +411,9 @@ struct ModeT<PF_F32> {
     }
     static __device__ __forceinline__ int cell(Val v, int origin, int lo, int hi)
     {
-        return offset_cell((float)v, origin, lo, hi);
+        return origin + min(max(round_half_up(v), lo - origin), hi - origin);
     }
+    static __device__ __forceinline__ int cell_near(Val v) { return round_half_up(v); }
 };
 
 // Half: two particles per 32-bit register; the propagation is one packed
@@ -468,16 +523,11 @@ struct ModeT<PF_F16> {
             y[i] = oy;
         }
     }
-    // A half's value in float, plus one half, is exact (at most 18
-    // significant bits), so floor(v + 1/2) is the half-up rounding that
-    // offset_cell forms in general; clamping v + 1/2 to the integers
-    // [lo - origin, hi - origin] before the floor clamps the cell to
-    // [lo, hi] (floor commutes with a clamp to integers).
     static __device__ __forceinline__ int cell(Val v, int origin, int lo, int hi)
     {
-        const float f = __builtin_amdgcn_fmed3f((float)v + 0.5f, (float)(lo - origin), (float)(hi - origin));
-        return origin + (int)floorf(f);
+        return origin + min(max(round_half_up((float)v), lo - origin), hi - origin);
     }
+    static __device__ __forceinline__ int cell_near(Val v) { return round_half_up((float)v); }
 };
 
 // bfloat16: gfx950 has no packed bfloat16 multiply-add, so the state is
@@ -557,8 +607,9 @@ struct ModeT<PF_BF16> {
     }
     static __device__ __forceinline__ int cell(Val v, int origin, int lo, int hi)
     {
-        return offset_cell((float)v, origin, lo, hi);
+        return origin + min(max(round_half_up(v), lo - origin), hi - origin);
     }
+    static __device__ __forceinline__ int cell_near(Val v) { return round_half_up(v); }
 };
 
 template <int DT>
@@ -590,6 +641,7 @@ struct PassALds {
     double red_d[3][kMaxWavesA];
     float red_f[3][kMaxWavesA];
     int red_i[kMaxWavesA];
+    alignas(4) uint8_t hw[2 * kMaxRadius];  // half widths of the disk's rows (run-time radius)
 };
 
 // Source tiles whose prefix sums and propagated positions a gathered state
@@ -624,6 +676,120 @@ union PassAGatherLds {
 template <int DT, int PPT, typename Pre>
 __device__ void gather_state(const StepArgs& a, int tile, bool prev_odd, GatherLds<DT>& lds, const int* ev,
                              typename ModeT<DT>::Val* x, typename ModeT<DT>::Val* y, Pre&& pre);
+
+// A thread's PPT consecutive tile prefix sums.
+template <int DT, int PPT, bool WT, typename Acc>
+__device__ __forceinline__ void store_q(void* out, int k0, const Acc (&q)[PPT])
+{
+    if constexpr (DT == PF_F64) {
+        auto* qp = gbl(reinterpret_cast<double2_t*>(static_cast<double*>(out) + k0));
+#pragma unroll
+        for (int i = 0; i < PPT / 2; ++i) put<WT>(qp + i, double2_t{q[2 * i], q[2 * i + 1]});
+    } else {
+        auto* qp = gbl(reinterpret_cast<float2_t*>(static_cast<float*>(out) + k0));
+        if constexpr (WT && PPT % 4 == 0) {  // one 16-byte store per four particles
+#pragma unroll
+            for (int i = 0; i < PPT / 4; ++i)
+                put16_wt(reinterpret_cast<gbl_t<u32x4_t>*>(qp) + i,
+                         u32x4_t{__float_as_uint(q[4 * i]), __float_as_uint(q[4 * i + 1]),
+                                 __float_as_uint(q[4 * i + 2]), __float_as_uint(q[4 * i + 3])});
+        } else {
+#pragma unroll
+            for (int i = 0; i < PPT / 2; ++i) put<WT>(qp + i, float2_t{q[2 * i], q[2 * i + 1]});
+        }
+    }
+}
+
+// Frame window of a box of pixel cells [bx0, bx1] x [by0, by1]: the pixels
+// that the disks around them reach.
+struct FrameWindow {
+    int xs, wy0;    // frame column of table column 0, frame row of table row 0
+    int sh;         // table column of the box's first disk pixel
+    int tw, wh;     // table columns and rows
+    bool aligned;   // the frame's rows are 4-byte aligned
+    __device__ bool fits() const { return tw <= kWinMaxW && wh <= kPrefRows; }
+};
+
+__device__ __forceinline__ FrameWindow frame_window(const StepArgs& a, int r, int bx0, int by0, int bx1, int by1)
+{
+    FrameWindow w;
+    const int wx0 = bx0 - (r - 1);
+    w.wy0 = by0 - (r - 1);
+    w.aligned = ((reinterpret_cast<uintptr_t>(a.frame) | (uintptr_t)a.pitch) & 3) == 0;
+    w.xs = w.aligned ? (wx0 & ~3) : wx0;
+    w.sh = wx0 - w.xs;
+    w.tw = bx1 - bx0 + 2 * r - 1 + w.sh;
+    w.wh = by1 - by0 + 2 * r - 1;
+    return w;
+}
+
+// The window's row-prefix table in LDS, built by NW waves.  A window row is
+// split over LPR lanes (16 for windows up to 64 columns, else 32), four
+// columns per lane, so a wave covers 64 / LPR rows per round; every load of
+// the wave is issued before the first scan, and each lane writes its four
+// prefix values as two 32-bit LDS stores.  When the frame's rows are 4-byte
+// aligned the table starts at the window's first column rounded down to a
+// multiple of 4, so a lane whose four columns lie inside the frame reads them
+// with one aligned 32-bit load (edge lanes read bytes, clamped to the frame).
+// Columns past the window only reach prefix entries no disk reads.
+template <int NW>
+__device__ __forceinline__ void fill_row_prefix(const StepArgs& a, const FrameWindow& win, uint16_t* pref, int wv,
+                                                int lane)
+{
+    constexpr int kMaxRounds = kPrefRows / (NW * 2);  // 32-lane rows: 2 per wave per round
+    const bool narrow = win.tw <= 64;
+    const int lpr = narrow ? 16 : 32;
+    const int rpr = 64 / lpr;                 // rows per wave per round
+    const int sub = lane / lpr, l = lane - sub * lpr;
+    const int c0 = 4 * l;
+    const int rows_per_round = NW * rpr;
+    const int rounds = (win.wh + rows_per_round - 1) / rows_per_round;
+    uint32_t v[kMaxRounds];
+#pragma unroll
+    for (int it = 0; it < kMaxRounds; ++it) {
+        const int yy = (it * NW + wv) * rpr + sub;
+        v[it] = 0;
+        if (it < rounds && yy < win.wh && c0 < win.tw) {
+            const int row = min(max(win.wy0 + yy, 0), a.H - 1);
+            const auto* rp = gbl(a.frame + (int64_t)row * a.pitch);
+            const int x = win.xs + c0;
+            uint32_t pk = 0;
+            if (win.aligned && x >= 0 && x + 3 < a.W) {
+                pk = *reinterpret_cast<const gbl_t<uint32_t>*>(rp + x);
+            } else {
+#pragma unroll
+                for (int bb = 0; bb < 4; ++bb)
+                    pk |= (uint32_t)rp[min(max(x + bb, 0), a.W - 1)] << (8 * bb);
+            }
+            v[it] = pk;
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < kMaxRounds; ++it) {
+        if (it < rounds) {  // uniform: every lane takes part in the scan
+            const int yy = (it * NW + wv) * rpr + sub;
+            const int p1 = (int)(v[it] & 0xFF);
+            const int p2 = p1 + (int)((v[it] >> 8) & 0xFF);
+            const int p3 = p2 + (int)((v[it] >> 16) & 0xFF);
+            const int p4 = p3 + (int)(v[it] >> 24);
+            // inclusive prefix of the 4-column sums over the lanes of one row
+            int sc = p4;
+            sc += dpp<0x111>(sc, 0);
+            sc += dpp<0x112>(sc, 0);
+            sc += dpp<0x114>(sc, 0);
+            sc += dpp<0x118>(sc, 0);
+            if (!narrow) sc += dpp<0x142, 0xA>(sc, 0);
+            const int ex = sc - p4;
+            if (yy < win.wh) {
+                uint16_t* prow = pref + yy * kPrefPitch + kPrefBase;
+                if (l == 0) prow[0] = 0;
+                uint32_t* w32 = reinterpret_cast<uint32_t*>(prow + c0 + 1);
+                w32[0] = (uint32_t)(ex + p1) | ((uint32_t)(ex + p2) << 16);
+                w32[1] = (uint32_t)(ex + p3) | ((uint32_t)(ex + p4) << 16);
+            }
+        }
+    }
+}
 
 // Pass A of tile `tile` of the filter described by `a`, PPT particles per
 // thread (kTile / PPT threads).  GATHER: the filter defers its resampling
@@ -740,6 +906,7 @@ __device__ __forceinline__ void pass_a_tile(const StepArgs& a, int tile, PassALd
             b2 = min(b2, -cx[i]); b3 = min(b3, -cy[i]);
         }
     }
+    if constexpr (RC == 0) fill_half_widths(lds.hw, r);
     // Bounding box of the tile's cells: four wave reductions, one exchange.
     b0 = wave_min(b0); b1 = wave_min(b1); b2 = wave_min(b2); b3 = wave_min(b3);
     if (lane == 0) {
@@ -753,84 +920,21 @@ __device__ __forceinline__ void pass_a_tile(const StepArgs& a, int tile, PassALd
     }
     const int bx0 = b0, by0 = b1, bx1 = -b2, by1 = -b3;
 
-    // Disk sums over the frame window of the tile: the window's row-prefix
-    // table is built in LDS.  A window row is split over LPR lanes (16 for
-    // windows up to 64 columns, else 32), four columns per lane, so a wave
-    // covers 64 / LPR rows per round; every load of the wave is issued before
-    // the first scan, and each lane writes its four prefix values as two
-    // 32-bit LDS stores.  When the frame's rows are 4-byte aligned the table
-    // starts at the window's first column rounded down to a multiple of 4, so
-    // a lane whose four columns lie inside the frame reads them with one
-    // aligned 32-bit load (edge lanes read bytes, clamped to the frame).
-    // Columns past the window only reach prefix entries no disk reads.
-    const int wx0 = bx0 - (r - 1), wy0 = by0 - (r - 1);
-    const int ww = bx1 - bx0 + 2 * r - 1, wh = by1 - by0 + 2 * r - 1;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(a.frame) | (uintptr_t)a.pitch) & 3) == 0;
-    const int xs = aligned ? (wx0 & ~3) : wx0;  // frame column of table column 0
-    const int sh = wx0 - xs;
-    const int tw = ww + sh;                     // table columns
-    const bool in_lds = !a.naive_lik && tw <= kWinMaxW && wh <= kPrefRows;
+    // Disk sums through the row-prefix table of the tile's frame window.
+    const FrameWindow win = frame_window(a, r, bx0, by0, bx1, by1);
+    const bool in_lds = !a.naive_lik && win.tw <= kWinMaxW && win.wh <= kPrefRows;
     int S[PPT];
     if (in_lds) {
-        constexpr int kMaxRounds = kPrefRows / (kWavesA * 2);  // 32-lane rows: 2 per wave per round
-        const bool narrow = tw <= 64;
-        const int lpr = narrow ? 16 : 32;
-        const int rpr = 64 / lpr;                 // rows per wave per round
-        const int sub = lane / lpr, l = lane - sub * lpr;
-        const int c0 = 4 * l;
-        const int rows_per_round = kWavesA * rpr;
-        const int rounds = (wh + rows_per_round - 1) / rows_per_round;
-        uint32_t v[kMaxRounds];
-#pragma unroll
-        for (int it = 0; it < kMaxRounds; ++it) {
-            const int yy = (it * kWavesA + wv) * rpr + sub;
-            v[it] = 0;
-            if (it < rounds && yy < wh && c0 < tw) {
-                const int row = min(max(wy0 + yy, 0), a.H - 1);
-                const auto* rp = gbl(a.frame + (int64_t)row * a.pitch);
-                const int x = xs + c0;
-                uint32_t pk = 0;
-                if (aligned && x >= 0 && x + 3 < a.W) {
-                    pk = *reinterpret_cast<const gbl_t<uint32_t>*>(rp + x);
-                } else {
-#pragma unroll
-                    for (int bb = 0; bb < 4; ++bb)
-                        pk |= (uint32_t)rp[min(max(x + bb, 0), a.W - 1)] << (8 * bb);
-                }
-                v[it] = pk;
-            }
-        }
-#pragma unroll
-        for (int it = 0; it < kMaxRounds; ++it) {
-            if (it < rounds) {  // uniform: every lane takes part in the scan
-                const int yy = (it * kWavesA + wv) * rpr + sub;
-                const int p1 = (int)(v[it] & 0xFF);
-                const int p2 = p1 + (int)((v[it] >> 8) & 0xFF);
-                const int p3 = p2 + (int)((v[it] >> 16) & 0xFF);
-                const int p4 = p3 + (int)(v[it] >> 24);
-                // inclusive prefix of the 4-column sums over the lanes of one row
-                int sc = p4;
-                sc += dpp<0x111>(sc, 0);
-                sc += dpp<0x112>(sc, 0);
-                sc += dpp<0x114>(sc, 0);
-                sc += dpp<0x118>(sc, 0);
-                if (!narrow) sc += dpp<0x142, 0xA>(sc, 0);
-                const int ex = sc - p4;
-                if (yy < wh) {
-                    uint16_t* prow = lds.pref + yy * kPrefPitch + kPrefBase;
-                    if (l == 0) prow[0] = 0;
-                    uint32_t* w32 = reinterpret_cast<uint32_t*>(prow + c0 + 1);
-                    w32[0] = (uint32_t)(ex + p1) | ((uint32_t)(ex + p2) << 16);
-                    w32[1] = (uint32_t)(ex + p3) | ((uint32_t)(ex + p4) << 16);
-                }
-            }
-        }
+        fill_row_prefix<kWavesA>(a, win, lds.pref, wv, lane);
         __syncthreads();
+        int off[PPT];
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
-            const int ox = valid[i] ? cx[i] - bx0 + sh : 0, oy = valid[i] ? cy[i] - by0 : 0;
-            S[i] = disk_sum_prefix<RC>(lds.pref + oy * kPrefPitch + ox, r);
+            // (24-bit product: the full-rate multiply)
+            const int o = (int)__umul24((uint32_t)(cy[i] - by0), kPrefPitch) + cx[i] - bx0 + win.sh;
+            off[i] = valid[i] ? o : 0;
         }
+        disk_sums_prefix<RC, PPT>(lds.pref, off, S, r, lds.hw);
     } else {
 #pragma unroll
         for (int i = 0; i < PPT; ++i)
@@ -911,23 +1015,7 @@ __device__ __forceinline__ void pass_a_tile(const StepArgs& a, int tile, PassALd
         const Acc v = excl + loc[i];
         q[i] = v < incl ? v : incl;
     }
-    if constexpr (DT == PF_F64) {
-        auto* qp = gbl(reinterpret_cast<double2_t*>(static_cast<double*>(out_q) + k0));
-#pragma unroll
-        for (int i = 0; i < PPT / 2; ++i) put<WT>(qp + i, double2_t{q[2 * i], q[2 * i + 1]});
-    } else {
-        auto* qp = gbl(reinterpret_cast<float2_t*>(static_cast<float*>(out_q) + k0));
-        if constexpr (WT && PPT % 4 == 0) {  // one 16-byte store per four particles
-#pragma unroll
-            for (int i = 0; i < PPT / 4; ++i)
-                put16_wt(reinterpret_cast<gbl_t<u32x4_t>*>(qp) + i,
-                         u32x4_t{__float_as_uint(q[4 * i]), __float_as_uint(q[4 * i + 1]),
-                                 __float_as_uint(q[4 * i + 2]), __float_as_uint(q[4 * i + 3])});
-        } else {
-#pragma unroll
-            for (int i = 0; i < PPT / 2; ++i) put<WT>(qp + i, float2_t{q[2 * i], q[2 * i + 1]});
-        }
-    }
+    store_q<DT, PPT, WT>(out_q, k0, q);
     if (a.dg_s) {
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
@@ -954,6 +1042,18 @@ __device__ __forceinline__ void pass_a_tile(const StepArgs& a, int tile, PassALd
     }
 }
 
+// Wave priority by progress through a streaming workgroup's share: the further
+// behind, the higher (at equal priority the oldest wave issues first, and a
+// CU's workgroups would finish one after the other).
+__device__ __forceinline__ void prio_by_progress(int done, int total)
+{
+    const int q = 4 * done;
+    if (q < total) __builtin_amdgcn_s_setprio(3);
+    else if (q < 2 * total) __builtin_amdgcn_s_setprio(2);
+    else if (q < 3 * total) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
 // Tile of workgroup b when consecutive tiles should share an XCD: workgroups
 // are dispatched to the 8 XCDs in turn (b mod 8), and XCD x takes a
 // contiguous range of tiles (a bijection of [0, nt) for any nt).
@@ -975,6 +1075,411 @@ __global__ __launch_bounds__(kTile / PPT) void pass_a_kernel(StepArgs a)
         __shared__ PassALds lds;
         pass_a_tile<DT, RC, PPT, SCALAR_HALF, WT, GATHER>(a, blockIdx.x, lds);
     }
+}
+
+// ---------------------------------------------------------------------------
+// Pass A over a run of consecutive tiles of one filter by one workgroup.
+//
+// The particles of a filter look at few pixel cells: a move of deviation
+// (5, 2) spreads 1024 particles over ~500 cells, and every other tile over the
+// same ones.  So the workgroup keeps a table of cells in LDS, with each cell's
+// disk term S and its weight relative to a reference maximum, built once from
+// the row-prefix table of the cells' frame window; a particle then costs one
+// table read instead of 2 (2r - 1) reads of the row prefixes and an
+// exponential.  The table is bounded (kCells); it is built around the first
+// tile's cells with a margin for the later tiles' (a tile with a particle
+// outside it has it rebuilt around both), and tiles whose cells do not fit
+// take their sums from the row prefixes, or from the frame, as pass_a_tile
+// does.  The weights are used before the tile's maximum is known: the waves
+// exchange the maximum together with the sums of the weights, once per tile,
+// and only a tile whose maximum is not the table's reference forms its
+// weights from S and exchanges again.  Same operations on the same values in
+// the same order as pass_a_tile, so the same bits.
+//
+// Bound: vector issue.  Per wave and tile 446 vector and 24 LDS instructions
+// against pass_a_tile's 704 and 135 (r = 8), whose LDS was busy too (82 % of the
+// cycles, 48 % conflicts; now 14 %).  2^24 FP16 particles, r = 8: 85 -> 52 us;
+// the 4096-stream 256 x 256 batch 237 -> 182 us; 27 000 FP32 tiles of 192
+// streams with mixed radii 152 -> 79 us.  Six workgroups per CU: with seven or
+// eight (a smaller table, registers spilled) it was 4-8 % slower.
+//
+// The waves' issue priority falls with their progress.  Without it the oldest
+// waves ran first: of six resident workgroups the first ended after 21 us, the
+// last, alone on its CU, after 62; 2^24 particles 60 -> 52 us, the batch 205 ->
+// 182.  More, shorter workgroups instead (two rounds of them) gave half of that.
+//
+// The line lies at 4096 tiles, about three per workgroup: below, the first
+// tile's table costs what the later ones gain (FP16 us of pass A one-tile |
+// streaming: 2^21 r = 5 11.9 | 16.5, 3 2^20 15.5 | 18.4, 2^22 19.0 | 19.8, 2^22 r = 8
+// 24.3 | 21.4, 2^23 33.9 | 28.6).  The double mode does not stream: it is bound by
+// memory, and its one-tile pass needs half the registers (2^23 + 1 particles: 158
+// us a step against 165).
+constexpr int kStreamTiles = 4096;
+constexpr int kCells = 2048;      // cells of the table
+constexpr int kMaxTableBuilds = 6;  // per run; then every tile takes its sums from the row prefixes
+
+struct PassAStreamLds {
+    alignas(16) int32_t S[kCells];  // the table: disk terms ...
+    union {                         // ... and weights, where the row prefixes were
+        uint16_t pref[kPrefPitch * kPrefRows];
+        alignas(16) float W[kCells];
+    };
+    // one exchange per tile, in two alternating buffers: a wave writes the
+    // next tile's while others still read this one's
+    alignas(16) int32_t smax[2][kWavesA];
+    alignas(16) float sw[2][kWavesA];
+    alignas(16) float ex[2][kWavesA];
+    alignas(16) float ey[2][kWavesA];
+    alignas(16) int32_t box[kWavesA][4];
+    alignas(16) uint8_t hw[2 * kMaxRadius];
+};
+
+// Weight of a disk term relative to the maximum m.
+__device__ __forceinline__ float weight_of(int S, int m, float beta)
+{
+    return __builtin_amdgcn_exp2f((float)(S - m) * beta);
+}
+
+// Tiles [t0, t1) of one filter; `ap` points to its arguments (read where they
+// are needed: the slow part takes its own copy, so that the fast part's loop
+// holds only what it uses), frame and pitch are the step's, `par` alternates
+// the exchange buffers over the whole kernel.
+template <int DT, int RC, bool WT>
+__device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const uint8_t* frame, int64_t pitch, int t0,
+                                              int t1, int done, int total, PassAStreamLds& lds, int& par)
+{
+    using M = ModeT<DT>;
+    typedef float F4 __attribute__((ext_vector_type(4)));
+    static_assert(DT != PF_F64, "the double mode does not stream");
+    using Store = typename M::Store;
+    constexpr int PPT = kPPT;
+    static_assert(kWavesA == 4, "one wave's totals per component");
+    typedef int32_t I4 __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = (int)ap->n;
+
+    StepArgs a{};  // the fields that propagation and weights read
+    a.drift_x = ap->drift_x; a.drift_y = ap->drift_y; a.sigma_x = ap->sigma_x; a.sigma_y = ap->sigma_y;
+    a.stream_id = ap->stream_id;
+    const auto* blk = gbl(ap->blk);
+    const uint32_t tn = blk->t + 1u;
+    const int cnx = blk->cn_x, cny = blk->cn_y;
+    const float ddx = (float)(a.drift_x - (double)(cnx - blk->ci_x));
+    const float ddy = (float)(a.drift_y - (double)(cny - blk->ci_y));
+    const typename M::Prop pr = make_prop<DT>(a, ddx, ddy);
+    const uint32_t key0 = ap->key0, key1 = ap->key1;
+    const auto* sx = static_cast<const Store*>(ap->sx);
+    const auto* sy = static_cast<const Store*>(ap->sy);
+    auto* px = static_cast<Store*>(ap->px);
+    auto* py = static_cast<Store*>(ap->py);
+    auto* qb = static_cast<float*>(ap->q);
+    const bool keep = ap->dg_s != nullptr || ap->s_all != nullptr;
+
+    // the table's cells [bx, bx + bw) x [by, by + bh), counted from the origin
+    // cell (bw = 0: none), whether they reach a bound at which cells are
+    // clamped, the reference of its weights and the times it was built
+    int bx = 0, by = 0, bw = 0, bh = 0, ref = 0, builds = 0;
+    bool edge = false;
+
+    // the next tile's state is loaded a tile ahead; one wait for the first
+    // tile's here, so that the loop's wait for the next one's does not also
+    // wait for the stores issued after them
+    typename M::Val nx[PPT], ny[PPT];
+    M::template load<PPT>(sx + (int64_t)t0 * kTile, tid * PPT, nx);
+    M::template load<PPT>(sy + (int64_t)t0 * kTile, tid * PPT, ny);
+#pragma unroll
+    for (int i = 0; i < PPT; ++i) __asm__ volatile("" ::"v"(nx[i]), "v"(ny[i]));
+    for (int t = t0; t < t1; ++t) {
+        prio_by_progress(done + t - t0, total);
+        const int64_t tile0 = (int64_t)t * kTile;  // uniform
+        const int k0 = t * kTile + tid * PPT;
+        const bool full = (t + 1) * kTile <= n;  // uniform
+        typename M::Val x[PPT], y[PPT];
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) { x[i] = nx[i]; y[i] = ny[i]; }
+        const int64_t next0 = (int64_t)min(t + 1, t1 - 1) * kTile;
+        M::template load<PPT>(sx + next0, tid * PPT, nx);
+        M::template load<PPT>(sy + next0, tid * PPT, ny);
+        // the round keys are formed anew for each tile: kept over the loop
+        // they would hold twenty scalar registers
+        a.key0 = key0;
+        a.key1 = key1;
+        __asm__ volatile("" : "+s"(a.key0), "+s"(a.key1));
+        M::template propagate<PPT>(x, y, pr, a, k0, tn);
+        M::template store<PPT, WT>(px + tile0, tid * PPT, x);
+        M::template store<PPT, WT>(py + tile0, tid * PPT, y);
+
+        // Sums of the tile's weights (wave scans and totals) as pass_a_tile
+        // forms them, published with the wave's maximum in buffer b.
+        float loc[PPT], sw;
+        int b = 0;
+        auto publish = [&](const float (&w)[PPT], int wmax) {
+            float run = 0, ex = 0, ey = 0;
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) {
+                run = run + w[i];
+                loc[i] = run;
+                ex = ex + w[i] * (float)x[i];
+                ey = ey + w[i] * (float)y[i];
+            }
+            sw = wave_incl_sum(run, lane);
+            sw = wave_incl_max_nonneg(sw);  // the weights are non-negative
+            ex = wave_sum(ex);
+            ey = wave_sum(ey);
+            b = par;
+            par ^= 1;
+            if (lane == 63) {
+                lds.smax[b][wv] = wmax;
+                lds.sw[b][wv] = sw;
+                lds.ex[b][wv] = ex;
+                lds.ey[b][wv] = ey;
+            }
+            __syncthreads();
+            const I4 m4 = *reinterpret_cast<const I4*>(lds.smax[b]);
+            return (int)__builtin_amdgcn_readfirstlane(max(max(m4.x, m4.y), max(m4.z, m4.w)));
+        };
+
+        int S[PPT];
+        float w[PPT];
+        int tile_max = INT32_MAX;
+        if (bw > 0) {
+            int ux[PPT], uy[PPT];
+            bool out = false;
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) {
+                ux[i] = M::cell_near(x[i]);
+                uy[i] = M::cell_near(y[i]);
+            }
+            if (edge) {  // uniform
+                const int r = RC > 0 ? RC : ap->r;
+                const int lox = -(r - 1) - cnx, hix = ap->W - 1 + (r - 1) - cnx;
+                const int loy = -(r - 1) - cny, hiy = ap->H - 1 + (r - 1) - cny;
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) {
+                    ux[i] = min(max(ux[i], lox), hix);
+                    uy[i] = min(max(uy[i], loy), hiy);
+                }
+            }
+            int wmax = INT32_MIN;
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) {
+                const uint32_t cx = (uint32_t)(ux[i] - bx), cy = (uint32_t)(uy[i] - by);
+                out = out | (cx >= (uint32_t)bw) | (cy >= (uint32_t)bh);
+                const uint32_t c = min(__umul24(cy, (uint32_t)bw) + cx, (uint32_t)(kCells - 1));
+                S[i] = lds.S[c];
+                w[i] = lds.W[c];
+            }
+            if (!full) {  // uniform: the filter's last tile
+                out = false;
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) {
+                    if (k0 + i < n) {
+                        out = out | ((uint32_t)(ux[i] - bx) >= (uint32_t)bw) | ((uint32_t)(uy[i] - by) >= (uint32_t)bh);
+                    } else {
+                        S[i] = INT32_MIN;
+                        w[i] = 0;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) wmax = max(wmax, S[i]);
+            wmax = wave_max(wmax);
+            if (__any(out)) wmax = INT32_MAX;  // a particle off the table
+            tile_max = publish(w, wmax);
+        }
+        if (bw == 0 || tile_max != ref) {
+            // the slow part: no table yet, a particle off it, or a tile with
+            // another maximum
+            const cst_t<StepArgs>* aq = ap;
+            __asm__ volatile("" : "+s"(aq));
+            StepArgs c{};
+            c.frame = frame; c.pitch = pitch;
+            c.W = aq->W; c.H = aq->H; c.r = aq->r; c.nd = aq->nd; c.fg = aq->fg; c.bg = aq->bg;
+            c.beta = aq->beta;
+            const int r = RC > 0 ? RC : c.r;
+            if (tile_max == INT32_MAX) {
+                // Cells are clamped where that changes none of the disk's pixels.
+                const int lox = -(r - 1) - cnx, hix = c.W - 1 + (r - 1) - cnx;
+                const int loy = -(r - 1) - cny, hiy = c.H - 1 + (r - 1) - cny;
+                const int c1k = 2 * (c.fg - c.bg), c0k = c.nd * (c.fg * c.fg - c.bg * c.bg);
+                int cx[PPT], cy[PPT];
+                int b0 = INT32_MAX, b1 = INT32_MAX, b2 = INT32_MAX, b3 = INT32_MAX;
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) {
+                    cx[i] = min(max(M::cell_near(x[i]), lox), hix);
+                    cy[i] = min(max(M::cell_near(y[i]), loy), hiy);
+                    if (k0 + i < n) {
+                        b0 = min(b0, cx[i]); b1 = min(b1, cy[i]);
+                        b2 = min(b2, -cx[i]); b3 = min(b3, -cy[i]);
+                    }
+                }
+                b0 = wave_min(b0); b1 = wave_min(b1); b2 = wave_min(b2); b3 = wave_min(b3);
+                if (lane == 0) *reinterpret_cast<I4*>(lds.box[wv]) = I4{b0, b1, b2, b3};
+                fill_half_widths(lds.hw, r);
+                __syncthreads();
+#pragma unroll
+                for (int v = 0; v < kWavesA; ++v) {
+                    const I4 o = *reinterpret_cast<const I4*>(lds.box[v]);
+                    b0 = min(b0, o.x); b1 = min(b1, o.y); b2 = min(b2, o.z); b3 = min(b3, o.w);
+                }
+                b0 = __builtin_amdgcn_readfirstlane(b0);
+                b1 = __builtin_amdgcn_readfirstlane(b1);
+                b2 = -__builtin_amdgcn_readfirstlane(b2);
+                b3 = -__builtin_amdgcn_readfirstlane(b3);
+                // the table's box: the tile's, widened for the tiles to come
+                // (the largest of some ten thousand normal draws lies about
+                // one deviation beyond that of 1024) and by the table so far;
+                // or else the tile's alone
+                // the margin is halved while the table does not fit
+                int x0, y0, x1, y1;
+                FrameWindow win;
+                auto frame_box = [&](int m, bool grow) {
+                    const int mx = ((int)(float)a.sigma_x + 1) * m >> 1, my = ((int)(float)a.sigma_y + 1) * m >> 1;
+                    x0 = max(b0 - mx, lox); x1 = min(b2 + mx, hix);
+                    y0 = max(b1 - my, loy); y1 = min(b3 + my, hiy);
+                    if (grow) {
+                        x0 = min(x0, bx); x1 = max(x1, bx + bw - 1);
+                        y0 = min(y0, by); y1 = max(y1, by + bh - 1);
+                    }
+                    x1 = x0 + ((x1 - x0) | 3);  // whole quads (the cells past the box are not used)
+                    win = frame_window(c, r, x0 + cnx, y0 + cny, x1 + cnx, y1 + cny);
+                    return win.fits() && (x1 - x0 + 1) * (y1 - y0 + 1) <= kCells;
+                };
+                bool table = false;
+                if (builds < kMaxTableBuilds) {
+                    const int m = t + 1 < t1 ? 2 : 0;
+                    table = bw > 0 && frame_box(m, true);
+                    for (int k = m; !table && k >= 0; --k) table = frame_box(k, false);
+                }
+                if (!table) {
+                    x0 = b0; y0 = b1; x1 = b2; y1 = b3;
+                    win = frame_window(c, r, x0 + cnx, y0 + cny, x1 + cnx, y1 + cny);
+                }
+                bw = 0;
+                if (win.fits()) {
+                    fill_row_prefix<kWavesA>(c, win, lds.pref, wv, lane);
+                    __syncthreads();
+                }
+                if (table) {
+                    ++builds;
+                    bx = x0; by = y0; bw = x1 - x0 + 1; bh = y1 - y0 + 1;
+                    edge = x0 <= lox || y0 <= loy || x1 >= hix || y1 >= hiy;
+                    // one cell per thread and round (with a run-time radius
+                    // four, which share the reads of the rows' half widths)
+                    constexpr int kM = RC > 0 ? 1 : 4;
+                    const int cells = bw * bh;
+                    int col = tid % bw, row = tid / bw;
+                    const int dq = kBlockA / bw, dr = kBlockA - dq * bw;
+#pragma unroll 1
+                    for (int j = tid; j < cells; j += kM * kBlockA) {
+                        int off[kM], s1[kM];
+#pragma unroll
+                        for (int m = 0; m < kM; ++m) {
+                            off[m] = j + m * kBlockA < cells ? row * kPrefPitch + col + win.sh : 0;
+                            row += dq;
+                            col += dr;
+                            if (col >= bw) { col -= bw; ++row; }
+                        }
+                        disk_sums_prefix<RC, kM>(lds.pref, off, s1, r, lds.hw);
+#pragma unroll
+                        for (int m = 0; m < kM; ++m)
+                            if (j + m * kBlockA < cells) lds.S[j + m * kBlockA] = c1k * s1[m] - c0k;
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int i = 0; i < PPT; ++i)
+                        S[i] = k0 + i < n ? lds.S[(cy[i] - by) * bw + cx[i] - bx] : INT32_MIN;
+                } else if (win.fits()) {
+                    int off[PPT], s4[PPT];
+#pragma unroll
+                    for (int i = 0; i < PPT; ++i)
+                        off[i] = k0 + i < n ? (cy[i] - y0) * kPrefPitch + cx[i] - x0 + win.sh : 0;
+                    disk_sums_rows<PPT>(lds.pref, off, s4, r, lds.hw);
+#pragma unroll
+                    for (int i = 0; i < PPT; ++i) S[i] = k0 + i < n ? c1k * s4[i] - c0k : INT32_MIN;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < PPT; ++i)
+                        S[i] = k0 + i < n ? c1k * disk_sum_global(frame, pitch, c.W, c.H, cx[i] + cnx, cy[i] + cny, r) - c0k
+                                          : INT32_MIN;
+                }
+                int wmax = wave_max(max(max(S[0], S[1]), max(S[2], S[3])));
+                b = par;
+                par ^= 1;
+                if (lane == 0) lds.smax[b][wv] = wmax;
+                __syncthreads();
+                const I4 m4 = *reinterpret_cast<const I4*>(lds.smax[b]);
+                tile_max = __builtin_amdgcn_readfirstlane(max(max(m4.x, m4.y), max(m4.z, m4.w)));
+                ref = INT32_MIN;  // no weights in the table yet
+            }
+#pragma unroll
+            for (int i = 0; i < PPT; ++i) w[i] = k0 + i < n ? weight_of(S[i], tile_max, c.beta) : (float)0;
+            publish(w, tile_max);
+            if (bw > 0 && tile_max > ref) {
+                // the table's weights, relative to the largest maximum so far
+                // (which later tiles most likely reach too)
+                ref = tile_max;
+                for (int j = 4 * tid; j < bw * bh; j += 4 * kBlockA) {
+                    const I4 s4 = *reinterpret_cast<const I4*>(lds.S + j);
+                    *reinterpret_cast<F4*>(lds.W + j) = F4{weight_of(s4.x, ref, c.beta), weight_of(s4.y, ref, c.beta),
+                                                           weight_of(s4.z, ref, c.beta), weight_of(s4.w, ref, c.beta)};
+                }
+                __syncthreads();
+            }
+        }
+
+        const F4 tot = *reinterpret_cast<const F4*>(lds.sw[b]);
+        float off = 0;
+        if (wv > 0) off = tot.x;
+        if (wv > 1) off = off + tot.y;
+        if (wv > 2) off = off + tot.z;
+        const float incl = wv > 0 ? off + sw : sw;
+        const float excl = wave_shift_up1(incl, off);
+        float q[PPT];
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) {
+            const float v = excl + loc[i];
+            q[i] = v < incl ? v : incl;
+        }
+        store_q<DT, PPT, WT>(qb + tile0, tid * PPT, q);
+        if (keep) {
+            const cst_t<StepArgs>* aq = ap;
+            __asm__ volatile("" : "+s"(aq));
+            if (aq->dg_s) {
+                auto *ds = gbl(aq->dg_s);
+                auto *dw = gbl(aq->dg_w);
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) {
+                    ds[k0 + i] = S[i];
+                    dw[k0 + i] = (double)w[i];
+                }
+            }
+            if (aq->s_all) {
+                auto* sa = gbl(aq->s_all);
+#pragma unroll
+                for (int i = 0; i < PPT; ++i) sa[k0 + i] = S[i];
+            }
+        }
+        if (tid == kBlockA - 1) {
+            // the tile total is the last thread's inclusive value
+            const F4 gx = *reinterpret_cast<const F4*>(lds.ex[b]), gy = *reinterpret_cast<const F4*>(lds.ey[b]);
+            const float tx = ((gx.x + gx.y) + gx.z) + gx.w, ty = ((gy.x + gy.y) + gy.z) + gy.w;
+            store_rec(gbl(static_cast<TileRec32*>(ap->rec)) + t, TileRec32{tile_max, incl, tx, ty});
+        }
+    }
+}
+
+// Workgroup b of G takes a contiguous share of the filter's tiles.
+template <int DT, int RC, bool WT>
+__global__ __launch_bounds__(kBlockA, 6) void pass_a_stream_kernel(StepArgs a)
+{
+    __shared__ PassAStreamLds lds;
+    int par = 0;
+    const int nt = a.ntiles, G = gridDim.x, b = blockIdx.x;
+    const auto* ap = (const cst_t<StepArgs>*)__builtin_amdgcn_kernarg_segment_ptr();  // `a` itself
+    const int t0 = (int)((int64_t)b * nt / G), t1 = (int)((int64_t)(b + 1) * nt / G);
+    pass_a_stream<DT, RC, WT>(ap, a.frame, a.pitch, t0, t1, 0, t1 - t0, lds, par);
 }
 
 // ---------------------------------------------------------------------------
@@ -2448,19 +2953,6 @@ __global__ __launch_bounds__(kBlock) void fill_kernel(Store* x, Store* y, int64_
 // code of the single-filter kernels on its filter's arguments, so a filter's
 // results do not depend on the batch it runs in.
 
-// The batch's plan (filter arguments, entries, tile map) does not change while
-// a kernel runs, so the kernels read it through the constant address space:
-// its uniform reads become scalar loads, which wait on their own counter (a
-// tile's arguments can arrive while vector loads of its inputs are in flight)
-// and come through the scalar cache.
-template <typename T>
-using cst_t = __attribute__((address_space(4))) T;
-template <typename T>
-__device__ __forceinline__ const cst_t<T>* cst(const T* p)
-{
-    return (const cst_t<T>*)p;
-}
-
 __device__ __forceinline__ int tile_entry_of(const BatchArgs& b, int gt) { return cst(b.tile_entry)[gt]; }
 __device__ __forceinline__ int tile_base_of(const BatchArgs& b, int e) { return cst(b.entries)[e].tile_base; }
 
@@ -2491,6 +2983,31 @@ __global__ __launch_bounds__(kTile / PPT) void pass_a_batch_kernel(BatchArgs b)
     const int lt = gt - tile_base_of(b, e);
     if (lt >= a.ntiles) return;  // a plan captured before the filter was re-initialised smaller
     pass_a_tile<DT, RC, PPT>(a, lt, lds);
+}
+
+// The streaming pass A over grid tiles (all, or the listed ones) of members of
+// the default pass-A size: each workgroup takes a contiguous share, run by run
+// of one member's tiles (a member's tiles follow each other in the grid and in
+// the list).  Tiles past a member's own (a plan captured before it was
+// re-initialised smaller) are passed over.
+template <int DT, int RC>
+__global__ __launch_bounds__(kBlockA, 6) void pass_a_batch_stream_kernel(BatchArgs b)
+{
+    __shared__ PassAStreamLds lds;
+    int par = 0;
+    const int G = gridDim.x, g = blockIdx.x;
+    const int i0 = (int)((int64_t)g * b.tiles / G);
+    int i = i0;
+    const int i1 = (int)((int64_t)(g + 1) * b.tiles / G);
+    while (i < i1) {
+        const int gt = b.a_tiles ? cst(b.a_tiles)[b.entry0 + i] : i;
+        const cst_t<BatchEntry>* en = cst(b.entries) + tile_entry_of(b, gt);
+        const cst_t<StepArgs>* ap = cst(b.args) + en->fid;
+        const int lt = gt - en->tile_base, run = min(en->tiles - lt, i1 - i);
+        const int t1 = min(lt + run, (int)ap->ntiles);
+        if (lt < t1) pass_a_stream<DT, RC, false>(ap, en->frame, en->pitch, lt, t1, i - i0, i1 - i0, lds, par);
+        i += run;
+    }
 }
 
 template <int DT, int KPER, int NT>
@@ -2616,6 +3133,34 @@ static hipError_t launch1(void (*kernel)(Arg), dim3 g, dim3 b, hipStream_t s, co
     return hipGetLastError();
 }
 
+// Workgroups of `kernel` (BC threads) resident on the whole device: the
+// grid of a streaming pass C (more would only queue behind the first ones).
+template <typename K>
+static int resident_cap(K kernel, int threads)
+{
+    int dev = 0, cus = 0, occ = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, 0) != hipSuccess || occ < 1 || cus < 1)
+        return 1 << 30;  // unknown: one tile per workgroup
+    return occ * cus;
+}
+
+template <int DT, int RC, bool WT>
+static hipError_t launch_pass_a_stream_r(const StepArgs& a, hipStream_t s, const KTiming& tm)
+{
+    static const int cap = resident_cap(pass_a_stream_kernel<DT, RC, WT>, kBlockA);
+    return launch1(pass_a_stream_kernel<DT, RC, WT>, dim3((unsigned)min(a.ntiles, cap)), dim3(kBlockA), s, tm, a);
+}
+
+template <int DT, bool WT>
+static hipError_t launch_pass_a_stream(const StepArgs& a, hipStream_t s, const KTiming& tm)
+{
+    if (a.r == 5) return launch_pass_a_stream_r<DT, 5, WT>(a, s, tm);
+    if (a.r == 8) return launch_pass_a_stream_r<DT, 8, WT>(a, s, tm);
+    return launch_pass_a_stream_r<DT, 0, WT>(a, s, tm);
+}
+
 template <int DT>
 static hipError_t launch_pass_a_t(const StepArgs& a, hipStream_t s, const KTiming& tm)
 {
@@ -2646,6 +3191,10 @@ static hipError_t launch_pass_a_t(const StepArgs& a, hipStream_t s, const KTimin
     }
     }
     if constexpr (DT != PF_F64) {
+        if (a.ntiles >= kStreamTiles && !a.naive_lik && !a.naive_half)
+            return a.wt ? launch_pass_a_stream<DT, true>(a, s, tm) : launch_pass_a_stream<DT, false>(a, s, tm);
+    }
+    if constexpr (DT != PF_F64) {
         if (a.wt && !a.naive_half) {  // a short step: outputs written through the L2
             if (a.r == 5) return launch1(pass_a_kernel<DT, 5, kPPT, false, true>, g, blk, s, tm, a);
             if (a.r == 8) return launch1(pass_a_kernel<DT, 8, kPPT, false, true>, g, blk, s, tm, a);
@@ -2672,19 +3221,6 @@ static hipError_t launch_naive_res(const StepArgs& a, hipStream_t s, const KTimi
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch1(resample_naive_kernel<DT, TPB>, dim3((unsigned)((a.n + TPB - 1) / TPB)), dim3(TPB), s, tm, a);
-}
-
-// Workgroups of `kernel` (BC threads) resident on the whole device: the
-// grid of a streaming pass C (more would only queue behind the first ones).
-template <typename K>
-static int resident_cap(K kernel, int threads)
-{
-    int dev = 0, cus = 0, occ = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, threads, 0) != hipSuccess || occ < 1 || cus < 1)
-        return 1 << 30;  // unknown: one tile per workgroup
-    return occ * cus;
 }
 
 template <int DT, int BC>
@@ -2781,10 +3317,26 @@ hipError_t launch_pass_c(int dtype, const StepArgs& a, hipStream_t s, const KTim
     PF_DISPATCH(dtype, launch_pass_c_t<DT>(a, s, tm))
 }
 
+template <int DT, int RC>
+static hipError_t launch_batch_stream(const BatchArgs& b, hipStream_t s, const KTiming& tm)
+{
+    static const int cap = resident_cap(pass_a_batch_stream_kernel<DT, RC>, kBlockA);
+    return launch1(pass_a_batch_stream_kernel<DT, RC>, dim3((unsigned)min(b.tiles, cap)), dim3(kBlockA), s, tm, b);
+}
+
 template <int DT, int PPT>
 static hipError_t launch_batch_pass_a_p(int rc, const BatchArgs& b, int tiles, hipStream_t s, const KTiming& tm)
 {
     const dim3 g((unsigned)tiles), blk(kTile / PPT);
+    if constexpr (DT != PF_F64 && PPT == kPPT) {
+        if (tiles >= kStreamTiles) {
+            BatchArgs bb = b;
+            bb.tiles = tiles;
+            if (rc == 5) return launch_batch_stream<DT, 5>(bb, s, tm);
+            if (rc == 8) return launch_batch_stream<DT, 8>(bb, s, tm);
+            return launch_batch_stream<DT, 0>(bb, s, tm);
+        }
+    }
     if (rc == 5) return launch1(pass_a_batch_kernel<DT, 5, PPT>, g, blk, s, tm, b);
     if (rc == 8) return launch1(pass_a_batch_kernel<DT, 8, PPT>, g, blk, s, tm, b);
     return launch1(pass_a_batch_kernel<DT, 0, PPT>, g, blk, s, tm, b);

@@ -268,7 +268,7 @@ struct BatchEntry {
     int32_t fid;        // index of the filter's StepArgs in the batch
     int32_t tile_base;  // first tile of the filter in the step's grid
     uint32_t t;         // index of the step
-    int32_t pad;
+    int32_t tiles;      // the filter's tiles in the step's grid
 };
 static_assert(sizeof(BatchEntry) == 32, "BatchEntry layout");
 
@@ -284,7 +284,7 @@ struct BatchArgs {
                              // (null: workgroup g takes grid tile g)
     int32_t entry0;     // combine: entry of the launch's first workgroup;
                         // listed pass A: index in a_tiles of its first tile
-    int32_t tiles;      // pass C: tiles of the step's grid (set by its launcher)
+    int32_t tiles;      // streaming passes: the launch's tiles (set by the launcher)
 };
 
 // Optional timing of one launch: events stamped by the kernel's own dispatch
