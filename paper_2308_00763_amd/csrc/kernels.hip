@@ -2678,6 +2678,13 @@ __device__ __forceinline__ void pass_c_run(const StepArgs& a, int t, PassCLds<DT
     }
 }
 
+// Whether a streaming pass C ranks its waves by progress: in the 16-bit modes,
+// whose pass C is bound by vector issue as much as by memory (2^24 particles
+// 38 -> 35 us, the 4096-stream batch 144 -> 136); in FP32 and FP64, bound by
+// memory, it costs 1 %.
+template <int DT>
+constexpr bool kPrioC = DT == PF_F16 || DT == PF_BF16;
+
 // Pass C of one filter over a grid of G <= ntiles workgroups: workgroup g
 // takes tiles g, g + G, ... and loads each tile's inputs while it scatters
 // the one before, so a workgroup's memory latency overlaps its own slot fill.
@@ -2693,7 +2700,9 @@ __global__ __launch_bounds__(BC, BC >= 256 ? 8 : 1) void pass_c_kernel(StepArgs 
     cur.load(a, t);
     cur.settle();  // one wait for the first tile's words and inputs
     TileSlotsT<DT> ts(r0);
-    for (;;) {
+    const int total = (nt - (int)blockIdx.x + G - 1) / G;
+    for (int done = 0;; ++done) {
+        if constexpr (kPrioC<DT> && !WT) prio_by_progress(done, total);
         const int tn = t + G;
         // the next tile's table words and inputs are loaded now and used
         // after this tile's scatter
@@ -3078,7 +3087,10 @@ __global__ __launch_bounds__(pass_c_threads(DT, 1 << 30), 8) void pass_c_batch_k
         base2 = tile_base_of(b, e);
     }
     if (g0 + 3 * G < T) e3 = tile_entry_of(b, g0 + 3 * G);
-    for (int g = g0;; g += G) {
+    const int total = (T - g0 + G - 1) / G;
+    int done = 0;
+    for (int g = g0;; g += G, ++done) {
+        if constexpr (kPrioC<DT>) prio_by_progress(done, total);
         const int g1 = g + G, g2 = g + 2 * G, g3 = g + 3 * G, g4 = g + 4 * G;
         typename TileSlotsT<DT>::Raw rn;
         PassCIn<DT, BC> nxt;
