@@ -8,6 +8,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -693,21 +694,35 @@ int pf_estimate_async(pf_filter* h, double* d_out_xy)
     return ok();
 }
 
+// Both coordinates are copied before the one wait; the double mode's straight
+// into the caller's arrays.
 static int export_positions(pf_filter* h, size_t off_x, size_t off_y, double* x, double* y, const DevBlock& b)
 {
     const int64_t n = h->p.n_particles;
     const int dt = h->p.dtype;
     const size_t bytes = (size_t)n * (size_t)elt_of(dt);
-    std::vector<uint8_t> buf(bytes);
     const size_t offs[2] = {off_x, off_y};
     double* dst[2] = {x, y};
-    const double org[2] = {dt == PF_F64 ? 0.0 : (double)b.ci_x, dt == PF_F64 ? 0.0 : (double)b.ci_y};
+    if (!x && !y) return PF_OK;
+    std::unique_ptr<uint8_t[]> buf;
+    if (dt != PF_F64) {
+        buf.reset(new (std::nothrow) uint8_t[2 * bytes]);
+        if (!buf) return fail(PF_ERR_INVALID_ARG, "out of host memory");
+    }
+    hipError_t e = hipSuccess;
+    for (int c = 0; c < 2 && e == hipSuccess; ++c) {
+        if (!dst[c]) continue;
+        void* to = dt == PF_F64 ? (void*)dst[c] : (void*)(buf.get() + c * bytes);
+        e = hipMemcpyAsync(to, at(h, offs[c]), bytes, hipMemcpyDeviceToHost, h->stream);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) return hip_fail(h, e, "export");
+    if (dt == PF_F64) return PF_OK;
+    const double org[2] = {(double)b.ci_x, (double)b.ci_y};
     for (int c = 0; c < 2; ++c) {
         if (!dst[c]) continue;
-        hipError_t e = hipMemcpyAsync(buf.data(), at(h, offs[c]), bytes, hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "export");
-        for (int64_t k = 0; k < n; ++k) dst[c][k] = org[c] + from_store(dt, buf.data(), k);
+        const uint8_t* src = buf.get() + c * bytes;
+        for (int64_t k = 0; k < n; ++k) dst[c][k] = org[c] + from_store(dt, src, k);
     }
     return PF_OK;
 }
@@ -741,7 +756,7 @@ static int materialize(pf_filter* h, DevBlock* b)
     hipError_t e = launch_pass_c(h->p.dtype, a, h->stream);
     if (e == hipSuccess) {
         b->pend = 0;
-        e = write_block(h, *b);
+        e = launch_clear_pend(a, h->stream);
     }
     if (e != hipSuccess) return hip_fail(h, e, "resampling of the latest step");
     return PF_OK;

@@ -3523,6 +3523,14 @@ hipError_t launch_diag_weights(int dtype, const StepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+__global__ void clear_pend_kernel(DevBlock* blk) { blk->pend = 0; }
+
+hipError_t launch_clear_pend(const StepArgs& a, hipStream_t s)
+{
+    clear_pend_kernel<<<1, 1, 0, s>>>(a.blk);
+    return hipGetLastError();
+}
+
 // vx, vy: the stored value of every particle (absolute in F64, the offset
 // from the origin cell in the reduced modes); converted to the storage type
 // with one rounding to nearest even.

@@ -308,6 +308,8 @@ hipError_t launch_combine(int dtype, const StepArgs& a, hipStream_t s, const KTi
 hipError_t launch_pass_c(int dtype, const StepArgs& a, hipStream_t s, const KTiming& tm = KTiming());
 hipError_t launch_fill(int dtype, const StepArgs& a, double vx, double vy, hipStream_t s);
 hipError_t launch_diag_weights(int dtype, const StepArgs& a, hipStream_t s);
+// Clears the block's pend flag (a pending resampling has been run).
+hipError_t launch_clear_pend(const StepArgs& a, hipStream_t s);
 // Batched passes: pass A and pass C over `tiles` grid tiles, the combine over
 // `count` entries of one combine class starting at b.entry0.  rc: the common
 // disk radius of the batch when it is 5 or 8, else 0.  Pass A runs the
