@@ -1081,7 +1081,8 @@ int pf_batch_init_cap(const pf_params* ps, int32_t n, int64_t max_tiles, void* d
         b->slot_bytes[k] = h->L.total;
         b->tiles_used += h->L.ntiles;
     }
-    b->stage_bytes = sizeof(BatchEntry) * (size_t)n + 8 * (size_t)bl.tiles;
+    // (the lists start at multiples of 8 bytes)
+    b->stage_bytes = sizeof(BatchEntry) * (size_t)n + 8 * (((size_t)bl.tiles + 1) & ~(size_t)1);
     hipError_t e = hipSuccess;
     for (int i = 0; i < kRing && e == hipSuccess; ++i) {
         e = hipHostMalloc((void**)&b->h_stage[i], b->stage_bytes, hipHostMallocDefault);
@@ -1155,7 +1156,7 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
     }
     BatchEntry* ent = reinterpret_cast<BatchEntry*>(stage);
     int32_t* tmap = reinterpret_cast<int32_t*>(stage + sizeof(BatchEntry) * (size_t)n);
-    int32_t* alist = tmap + b->total_tiles;
+    int32_t* alist = tmap + ((b->total_tiles + 1) & ~(int64_t)1);
     int32_t cls_begin[kCombClasses + 1];
     int32_t ne = 0, tiles = 0;
     for (int c = 0; c < kCombClasses; ++c) {
@@ -1201,11 +1202,14 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
     BatchEntry* d_ent = capturing ? b->d_g_entries : b->d_entries;
     int32_t* d_map = capturing ? b->d_g_tile_entry : b->d_tile_entry;
     int32_t* d_alist = capturing ? b->d_g_a_tiles : b->d_a_tiles;
-    e = hipMemcpyAsync(d_ent, ent, sizeof(BatchEntry) * (size_t)ne, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess && !same)
-        e = hipMemcpyAsync(d_map, tmap, 4 * (size_t)tiles, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess && !same && sizes_used > 1)
-        e = hipMemcpyAsync(d_alist, alist, 4 * (size_t)tiles, hipMemcpyHostToDevice, b->stream);
+    // One kernel reads the plan from the pinned staging buffer: as copies, each
+    // part waited some 20 us for its engine (4096 members, 131 KB: 23 us between
+    // two steps' kernels, 7 by the kernel).
+    PlanUpload up{};
+    up.part[0] = {d_ent, ent, (uint32_t)(sizeof(BatchEntry) / 8) * (uint32_t)ne};
+    if (!same) up.part[1] = {d_map, tmap, ((uint32_t)tiles + 1) / 2};
+    if (!same && sizes_used > 1) up.part[2] = {d_alist, alist, ((uint32_t)tiles + 1) / 2};
+    e = launch_upload(up, b->stream);
     if (e == hipSuccess && !capturing) e = hipEventRecord(b->ev[slot], b->stream);
     if (e == hipSuccess && !capturing) b->ev_used[slot] = true;
     BatchArgs ba;

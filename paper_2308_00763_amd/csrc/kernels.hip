@@ -3212,6 +3212,20 @@ __global__ __launch_bounds__(pass_c_threads(DT, 1 << 30), 8) void pass_c_batch_k
     }
 }
 
+// The plan's parts, loaded past the caches (the host rewrites the staging
+// buffer every third step).
+__global__ __launch_bounds__(kBlock) void upload_kernel(PlanUpload u)
+{
+    const uint32_t i0 = blockIdx.x * kBlock + threadIdx.x, step = gridDim.x * kBlock;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const auto* src = gbl(static_cast<const uint64_t*>(u.part[k].src));
+        auto* dst = gbl(static_cast<uint64_t*>(u.part[k].dst));
+        for (uint32_t i = i0; i < u.part[k].words; i += step)
+            dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void gather_est_kernel(const StepArgs* args, int n, double* out)
 {
     const int k = blockIdx.x * kBlock + threadIdx.x;
@@ -3494,6 +3508,13 @@ static hipError_t launch_batch_pass_c_t(const BatchArgs& b, int tiles, hipStream
 hipError_t launch_batch_pass_c(int dtype, const BatchArgs& b, int tiles, hipStream_t s, const KTiming& tm)
 {
     PF_DISPATCH(dtype, launch_batch_pass_c_t<DT>(b, tiles, s, tm))
+}
+
+hipError_t launch_upload(const PlanUpload& u, hipStream_t s)
+{
+    const uint32_t most = max(u.part[0].words, max(u.part[1].words, u.part[2].words));
+    upload_kernel<<<dim3(min((most + kBlock - 1) / kBlock, 256u)), dim3(kBlock), 0, s>>>(u);
+    return hipGetLastError();
 }
 
 hipError_t launch_gather_est(const StepArgs* args, int n, double* out, hipStream_t s)

@@ -287,6 +287,16 @@ struct BatchArgs {
     int32_t tiles;      // streaming passes: the launch's tiles (set by the launcher)
 };
 
+// Parts of a batched step's plan, from pinned host memory to the device (words
+// of 8 bytes; both sides 8-byte aligned and padded to whole words).
+struct PlanUpload {
+    struct Part {
+        void* dst;
+        const void* src;
+        uint32_t words;
+    } part[3];
+};
+
 // Optional timing of one launch: events stamped by the kernel's own dispatch
 // (start and end of its execution), no separate event records.
 struct KTiming {
@@ -321,6 +331,7 @@ hipError_t launch_batch_combine(int dtype, int cls, const BatchArgs& b, int coun
                                 const KTiming& tm = KTiming());
 hipError_t launch_batch_pass_c(int dtype, const BatchArgs& b, int tiles, hipStream_t s,
                                const KTiming& tm = KTiming());
+hipError_t launch_upload(const PlanUpload& u, hipStream_t s);
 // out[2k], out[2k+1] = estimate of filter k (device memory).
 hipError_t launch_gather_est(const StepArgs* args, int n, double* out, hipStream_t s);
 
