@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <math.h>
+#include <sched.h>
 #include <stdlib.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -72,8 +73,10 @@ struct pf_batch {
     std::vector<StepArgs> args_host; // host copy of the filters' StepArgs
     uint8_t* h_stage[kRing];
     uint8_t* h_graph;                 // staging read by the copies of a captured step
-    hipEvent_t ev[kRing];
-    bool ev_used[kRing];
+    // the step that last used a staging buffer: its pass C stores the number
+    // in `h_seen` (pinned), by when its upload has read the buffer
+    uint32_t* h_seen;
+    uint32_t step_no, slot_step[kRing];  // 0: not used yet
     int ring;
     size_t stage_bytes;
     std::vector<uint8_t> map_active;  // stepped set of the uploaded tile map
@@ -986,10 +989,10 @@ static void batch_free(pf_batch* b)
     }
     b->f.clear();
     for (int i = 0; i < kRing; ++i) {
-        if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
         if (b->h_stage[i]) (void)hipHostFree(b->h_stage[i]);
     }
     if (b->h_graph) (void)hipHostFree(b->h_graph);
+    if (b->h_seen) (void)hipHostFree(b->h_seen);
     delete b;
 }
 
@@ -1086,9 +1089,10 @@ int pf_batch_init_cap(const pf_params* ps, int32_t n, int64_t max_tiles, void* d
     hipError_t e = hipSuccess;
     for (int i = 0; i < kRing && e == hipSuccess; ++i) {
         e = hipHostMalloc((void**)&b->h_stage[i], b->stage_bytes, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
     }
     if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_graph, b->stage_bytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_seen, 64, hipHostMallocDefault);
+    if (e == hipSuccess) *b->h_seen = 0;
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_args, args.data(), sizeof(StepArgs) * (size_t)n, hipMemcpyHostToDevice, b->stream);
     for (int32_t k = 0; k < n && e == hipSuccess; ++k) {
@@ -1111,6 +1115,26 @@ static int batch_live(pf_batch* b)
     if (!b) return fail(PF_ERR_INVALID_ARG, "batch is NULL");
     if (b->poisoned) return fail(PF_ERR_STATE, "batch poisoned by an earlier HIP error");
     return PF_OK;
+}
+
+// Waits until the step that last used a staging buffer has read it: until the
+// number its pass C stores has come (the numbers only grow, so a later step's
+// will do), or the stream is found idle or failed.  An event per step would
+// put 6 us between the upload and pass A.
+static hipError_t wait_slot(pf_batch* b, int slot)
+{
+    const uint32_t want = b->slot_step[slot];
+    if (want == 0) return hipSuccess;
+    for (uint32_t spins = 1;; ++spins) {
+        if ((int32_t)(__atomic_load_n(b->h_seen, __ATOMIC_ACQUIRE) - want) >= 0) return hipSuccess;
+        if (spins % 256 == 0) sched_yield();
+        // (a query puts a marker into the stream: rarely)
+        if (spins % (1u << 17) == 0) {
+            const hipError_t e = hipStreamQuery(b->stream);
+            if (e != hipErrorNotReady) return e;
+        }
+        __builtin_ia32_pause();
+    }
 }
 
 int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pitches, const uint8_t* active)
@@ -1150,7 +1174,7 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
     uint8_t* stage = b->h_graph;
     if (!capturing) {
         b->ring = (b->ring + 1) % kRing;
-        if (b->ev_used[slot]) e = hipEventSynchronize(b->ev[slot]);
+        e = wait_slot(b, slot);
         if (e != hipSuccess) return batch_fail(b, e, "pf_batch_step");
         stage = b->h_stage[slot];
     }
@@ -1210,8 +1234,6 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
     if (!same) up.part[1] = {d_map, tmap, ((uint32_t)tiles + 1) / 2};
     if (!same && sizes_used > 1) up.part[2] = {d_alist, alist, ((uint32_t)tiles + 1) / 2};
     e = launch_upload(up, b->stream);
-    if (e == hipSuccess && !capturing) e = hipEventRecord(b->ev[slot], b->stream);
-    if (e == hipSuccess && !capturing) b->ev_used[slot] = true;
     BatchArgs ba;
     ba.args = b->d_args;
     ba.entries = d_ent;
@@ -1219,6 +1241,14 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
     ba.a_tiles = nullptr;
     ba.entry0 = 0;
     ba.tiles = tiles;
+    ba.seen = nullptr;
+    ba.step_no = 0;
+    if (!capturing) {
+        if (++b->step_no == 0) b->step_no = 1;
+        b->slot_step[slot] = b->step_no;
+        ba.seen = b->h_seen;
+        ba.step_no = b->step_no;
+    }
     for (int c = 0; c < 3 && e == hipSuccess; ++c) {
         if (a_count[c] == 0) continue;
         BatchArgs bp = ba;

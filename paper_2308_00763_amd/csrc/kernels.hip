@@ -3151,6 +3151,8 @@ __global__ __launch_bounds__(pass_c_threads(DT, 1 << 30), 8) void pass_c_batch_k
     __shared__ PassCLds<DT> lds;
     const int G = gridDim.x, T = b.tiles;
     const int g0 = blockIdx.x;  // < T: the grid has at most T workgroups
+    if (g0 == 0 && threadIdx.x == 0 && b.seen)  // the step's plan has been read
+        __hip_atomic_store(gbl(b.seen), b.step_no, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     // tile g0: everything now
     int e = tile_entry_of(b, g0);
     StepArgs a0 = batch_args_of(b, cst(b.entries)[e].fid);

@@ -285,6 +285,8 @@ struct BatchArgs {
     int32_t entry0;     // combine: entry of the launch's first workgroup;
                         // listed pass A: index in a_tiles of its first tile
     int32_t tiles;      // streaming passes: the launch's tiles (set by the launcher)
+    uint32_t step_no;   // pass C stores it in *seen (pinned host memory; may be null)
+    uint32_t* seen;
 };
 
 // Parts of a batched step's plan, from pinned host memory to the device (words
