@@ -2919,25 +2919,57 @@ __global__ __launch_bounds__(kBlock) void gumbel_kernel(StepArgs a)
 // FP32 particles tracking a disk: 380 -> 130 us; now bound by the gathers (one
 // line per lane).  At most 8 slots left instead of 16 measured the same, 32
 // 11 % more, 52 27 % more.
+//
+// Filters of at most kMaskParticles particles first mark, one bit each, the
+// particles that any acceptance word could accept (in a tracking step mostly
+// those of the best pixel cell, one in a hundred), and every workgroup keeps
+// the marks in LDS: a proposal without one is rejected without its gather.
+// 2^18 FP32 particles: 130 -> 65 us and 3 for the marks, which is mostly the
+// random words.
 constexpr int kFewSlots = 16;
+constexpr int kMaskParticles = 1 << 19;  // 64 KB of marks
 
+// Acceptance of a proposal of disk term Sc with acceptance word wu (monotone
+// in wu: what wu = 0 rejects, every word rejects).
 template <int DT>
-__global__ __launch_bounds__(kBlock) void rejection_kernel(StepArgs a)
+__device__ __forceinline__ bool rejection_accepts(const StepArgs& a, double M, int Smax, int Sc, uint32_t wu)
+{
+    if constexpr (DT == PF_F64)
+        return ((double)wu + 0.5) * 0x1.0p-32 <= exp((double)Sc / a.denom - M);
+    else
+        return ((float)(wu >> 8) + 0.5f) * 0x1.0p-24f <= __builtin_amdgcn_exp2f((float)(Sc - Smax) * a.beta);
+}
+
+// The marks go where the prefix sums were (the combine was their last reader).
+template <int DT>
+__global__ __launch_bounds__(kBlock) void rejection_mask_kernel(StepArgs a)
+{
+    const int j = blockIdx.x * kBlock + threadIdx.x;
+    const bool mark = j < (int)a.n && rejection_accepts<DT>(a, a.blk->M, a.blk->Smax, a.s_all[min(j, (int)a.n - 1)], 0u);
+    const uint64_t b = __ballot(mark);
+    if ((threadIdx.x & 63) == 0) static_cast<uint64_t*>(a.q)[j >> 6] = b;
+}
+
+// TB threads; MASK: the marks in dynamic LDS (one 64-bit word per 64 slots).
+template <int DT, int TB, bool MASK>
+__global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
 {
     using Store = typename ModeT<DT>::Store;
-    const int j = blockIdx.x * kBlock + threadIdx.x, lane = threadIdx.x & 63;
+    extern __shared__ uint32_t s_marks[];
+    const int j = blockIdx.x * TB + threadIdx.x, lane = threadIdx.x & 63;
     const int n = (int)a.n, cap = a.rj_cap;  // cap is even
     const auto* S = gbl(static_cast<const int32_t*>(a.s_all));
     const auto* blk = gbl(a.blk);
     const uint32_t t = blk->t;  // this step's index (the combine has advanced the count)
-    [[maybe_unused]] const double M = blk->M;
-    [[maybe_unused]] const int Smax = blk->Smax;
-    auto accepts = [&](int Sc, uint32_t wu) {
-        if constexpr (DT == PF_F64)
-            return ((double)wu + 0.5) * 0x1.0p-32 <= exp((double)Sc / a.denom - M);
-        else
-            return ((float)(wu >> 8) + 0.5f) * 0x1.0p-24f <= __builtin_amdgcn_exp2f((float)(Sc - Smax) * a.beta);
-    };
+    const double M = blk->M;
+    const int Smax = blk->Smax;
+    if constexpr (MASK) {
+        const auto* src = gbl(static_cast<const uint64_t*>(a.q));
+        for (int i = threadIdx.x; i < (n + 63) / 64; i += TB) reinterpret_cast<uint64_t*>(s_marks)[i] = src[i];
+        __syncthreads();
+    }
+    auto accepts = [&](int Sc, uint32_t wu) { return rejection_accepts<DT>(a, M, Smax, Sc, wu); };
+    auto marked = [&](int p) { return !MASK || ((s_marks[p >> 5] >> (p & 31)) & 1u) != 0; };
     auto words = [&](int slot, int pair) {
         return philox4x32_10((uint32_t)slot, t, a.stream_id, 2u + (uint32_t)pair, a.key0, a.key1);
     };
@@ -2963,7 +2995,7 @@ __global__ __launch_bounds__(kBlock) void rejection_kernel(StepArgs a)
     }
     while (m < cap && __popcll(__ballot(!done)) > kFewSlots) {  // the same for the wave
         if (!done) {
-            int p[kTrials + 1], s[kTrials];
+            int p[kTrials + 1];
             uint32_t wu[kTrials];
             p[0] = c;
 #pragma unroll
@@ -2974,15 +3006,39 @@ __global__ __launch_bounds__(kBlock) void rejection_kernel(StepArgs a)
                 wu[u + 1] = w.v2;
                 p[u + 2] = particle(w.v3);
             }
-#pragma unroll
-            for (int u = 0; u < kTrials; ++u) s[u] = S[p[u]];
             c = p[kTrials];
+            if constexpr (MASK) {
+                uint32_t left = 0;  // the marked trials
 #pragma unroll
-            for (int u = kTrials - 1; u >= 0; --u) {
-                if (m + u == cap - 1) c = p[u];  // the last trial's proposal is kept
-                if (m + u < cap && accepts(s[u], wu[u])) {
-                    c = p[u];
-                    done = true;
+                for (int u = 0; u < kTrials; ++u) {
+                    if (m + u == cap - 1) c = p[u];  // the last trial's proposal is kept
+                    if (m + u < cap && marked(p[u])) left |= 1u << u;
+                }
+                while (left && !done) {  // the first of them, mostly the only one
+                    const int f = __builtin_ctz(left);
+                    left &= left - 1;
+                    int pf = p[0];
+                    uint32_t wf = wu[0];
+#pragma unroll
+                    for (int u = 1; u < kTrials; ++u) {
+                        if (u == f) { pf = p[u]; wf = wu[u]; }
+                    }
+                    if (accepts(S[pf], wf)) {
+                        c = pf;
+                        done = true;
+                    }
+                }
+            } else {
+                int s[kTrials];
+#pragma unroll
+                for (int u = 0; u < kTrials; ++u) s[u] = S[p[u]];
+#pragma unroll
+                for (int u = kTrials - 1; u >= 0; --u) {
+                    if (m + u == cap - 1) c = p[u];
+                    if (m + u < cap && accepts(s[u], wu[u])) {
+                        c = p[u];
+                        done = true;
+                    }
                 }
             }
         }
@@ -2997,8 +3053,13 @@ __global__ __launch_bounds__(kBlock) void rejection_kernel(StepArgs a)
             const int p1 = particle(w.v1), p2 = particle(w.v3);
             const int p0 = wave_shift_up1(p2, carry);
             const bool in = mm + 2 * lane < cap;
-            const int s0 = S[p0], s1 = S[p1];
-            const bool a0 = in && accepts(s0, w.v0), a1 = in && accepts(s1, w.v2);
+            const bool m0 = in && marked(p0), m1 = in && marked(p1);
+            bool a0 = false, a1 = false;
+            if (m0 || m1) {
+                const int s0 = S[p0], s1 = S[p1];
+                a0 = m0 && accepts(s0, w.v0);
+                a1 = m1 && accepts(s1, w.v2);
+            }
             const uint64_t hit = __ballot(a0 || a1);
             if (hit) {
                 got = __builtin_amdgcn_readlane(a0 ? p0 : p1, __builtin_ctzll(hit));
@@ -3243,13 +3304,14 @@ __global__ __launch_bounds__(kBlock) void gather_est_kernel(const StepArgs* args
 // events take the start and end timestamps of the kernel's own execution.
 
 template <typename Arg>
-static hipError_t launch1(void (*kernel)(Arg), dim3 g, dim3 b, hipStream_t s, const KTiming& tm, Arg arg)
+static hipError_t launch1(void (*kernel)(Arg), dim3 g, dim3 b, hipStream_t s, const KTiming& tm, Arg arg,
+                          unsigned lds = 0)
 {
     if (tm.start || tm.stop) {
         void* args[] = {&arg};
-        return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), g, b, args, 0, s, tm.start, tm.stop, 0);
+        return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), g, b, args, lds, s, tm.start, tm.stop, 0);
     }
-    kernel<<<g, b, 0, s>>>(arg);
+    kernel<<<g, b, lds, s>>>(arg);
     return hipGetLastError();
 }
 
@@ -3356,14 +3418,31 @@ static hipError_t launch_pass_c_stream(const StepArgs& a, hipStream_t s, const K
     return launch1(pass_c_kernel<DT, BC>, dim3((unsigned)min(a.ntiles, cap)), dim3(BC), s, tm, a);
 }
 
+// With 64 KB of marks (2^19 particles) two workgroups fit a CU, hence the
+// larger ones past 2^18.
+template <int DT>
+static hipError_t launch_rejection(const StepArgs& a, hipStream_t s, const KTiming& tm)
+{
+    const dim3 g((unsigned)((a.n + kBlock - 1) / kBlock));
+    if (a.n > kMaskParticles) return launch1(rejection_kernel<DT, kBlock, false>, g, dim3(kBlock), s, tm, a);
+    KTiming t0, t1;
+    t0.start = tm.start;
+    t1.stop = tm.stop;
+    const hipError_t e = launch1(rejection_mask_kernel<DT>, g, dim3(kBlock), s, t0, a);
+    if (e != hipSuccess) return e;
+    const unsigned lds = (unsigned)((a.n + 63) / 64 * 8);
+    if (a.n > kMaskParticles / 2)
+        return launch1(rejection_kernel<DT, 1024, true>, dim3((unsigned)((a.n + 1023) / 1024)), dim3(1024), s, t1, a, lds);
+    return launch1(rejection_kernel<DT, kBlock, true>, g, dim3(kBlock), s, t1, a, lds);
+}
+
 template <int DT>
 static hipError_t launch_pass_c_t(const StepArgs& a, hipStream_t s, const KTiming& tm)
 {
     const dim3 g((unsigned)a.ntiles);
     if (a.mh_steps > 0)
         return launch1(metropolis_kernel<DT>, dim3((unsigned)((a.n + kBlock - 1) / kBlock)), dim3(kBlock), s, tm, a);
-    if (a.rj_cap > 0)
-        return launch1(rejection_kernel<DT>, dim3((unsigned)((a.n + kBlock - 1) / kBlock)), dim3(kBlock), s, tm, a);
+    if (a.rj_cap > 0) return launch_rejection<DT>(a, s, tm);
     if (a.gumbel)
         return launch1(gumbel_kernel<DT>, dim3((unsigned)((a.n + kBlock - 1) / kBlock)), dim3(kBlock), s, tm, a);
     if (a.naive_res) {
