@@ -856,26 +856,18 @@ __device__ __forceinline__ void pass_a_tile(const StepArgs& a, int tile, PassALd
             for (int j = 0; j < kEv; ++j) __asm__ volatile("" ::"v"(ev[j]));
         }
         if (blk->pend) {  // uniform
-            if constexpr (DT == PF_F64) {
-                // (drawn before, the double normals would hold 16 more
-                // registers through the gather: three workgroups per CU)
-                gather_state<DT, PPT>(a, tile, !odd, *glds, ev, x, y, []() {});
-                __syncthreads();  // the gather's LDS is the pass's from here on
-                M::template propagate<PPT>(x, y, pr, a, k0, tn);
-            } else {
-                // the normals are drawn while the candidates' loads are in
-                // flight (an empty use of each keeps the compiler from sinking
-                // the draws to their use after the gather)
-                typename M::template Noise<PPT> nz;
-                gather_state<DT, PPT>(a, tile, !odd, *glds, ev, x, y, [&]() {
-                    M::template draw<PPT>(nz, a, k0, tn);
-                    constexpr int kZ = (int)(sizeof(nz.zx) / sizeof(nz.zx[0]));
+            // the normals are drawn while the candidates' loads are in flight
+            // (an empty use of each keeps the compiler from sinking the draws
+            // to their use after the gather)
+            typename M::template Noise<PPT> nz;
+            gather_state<DT, PPT>(a, tile, !odd, *glds, ev, x, y, [&]() {
+                M::template draw<PPT>(nz, a, k0, tn);
+                constexpr int kZ = (int)(sizeof(nz.zx) / sizeof(nz.zx[0]));
 #pragma unroll
-                    for (int i = 0; i < kZ; ++i) __asm__ volatile("" ::"v"(nz.zx[i]), "v"(nz.zy[i]));
-                });
-                __syncthreads();  // the gather's LDS is the pass's from here on
-                M::template apply<PPT>(x, y, pr, nz);
-            }
+                for (int i = 0; i < kZ; ++i) __asm__ volatile("" ::"v"(nz.zx[i]), "v"(nz.zy[i]));
+            });
+            __syncthreads();  // the gather's LDS is the pass's from here on
+            M::template apply<PPT>(x, y, pr, nz);
         } else {
             M::template load<PPT>(a.sx, k0, x);
             M::template load<PPT>(a.sy, k0, y);
