@@ -436,6 +436,10 @@ void setup_filter(pf_filter* h, const pf_params& pr, uint8_t* ws, hipStream_t st
     // deferred resampling: at the default sizes (the gather assigns four slots
     // to each of 256 threads; a filter given a pass-C size wants its pass C)
     a.gather = L.px2 != 0 && a.threads_a == kBlockA && ((p->flags >> PF_THREADS_C_SHIFT) & 0xF) == 0 ? 1 : 0;
+    a.one = single && a.ntiles == 1 && a.threads_a == kBlockA && a.threads_c == 0 && !a.naive_lik && !a.naive_res &&
+                    !a.naive_half && !a.mh_steps && !a.rj_cap && !a.gumbel
+                ? 1
+                : 0;
     a.px2 = a.gather ? at(h, L.px2) : nullptr;
     a.py2 = a.gather ? at(h, L.py2) : nullptr;
     a.q2 = a.gather ? at(h, L.q2) : nullptr;

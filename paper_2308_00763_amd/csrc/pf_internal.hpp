@@ -255,6 +255,7 @@ struct StepArgs {
     // from the previous step's set, gathered through that step's table; the
     // combine writes the tiles' end slots to ecol as well and sets pend.
     int32_t gather;
+    int32_t one;        // a single filter of one tile at the default sizes, systematic: its step is one launch
     void* px2;
     void* py2;
     void* q2;
@@ -313,7 +314,8 @@ hipError_t static_scratch_setup(int device, uint8_t** out);
 
 // Host-side launchers (kernels.hip).  launch_step = launch_pass_a,
 // launch_combine, launch_pass_c on the same stream (no pass C for a filter
-// that defers its resampling).
+// that defers its resampling), or one launch with the same results
+// (StepArgs::one).
 hipError_t launch_step(int dtype, const StepArgs& a, hipStream_t s);
 hipError_t launch_pass_a(int dtype, const StepArgs& a, hipStream_t s, const KTiming& tm = KTiming());
 hipError_t launch_combine(int dtype, const StepArgs& a, hipStream_t s, const KTiming& tm = KTiming());
