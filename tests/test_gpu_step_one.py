@@ -65,3 +65,20 @@ def test_one_launch_in_a_graph(dtype):
     assert np.array_equal(u["x"], v["x"]) and np.array_equal(u["y"], v["y"])
     e.close()
     f.close()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "bf16"])
+def test_one_launch_on_the_static_scratch(dtype):
+    vid = pfsynth.moving_disk(128, 128, 5, 5, (64, 64), (1, -2), 3.0, 11)
+    fr = torch.from_numpy(vid.frames).to("cuda:0")
+    x0, y0 = vid.centres[0]
+    a = _filter(dtype, 1000, 5, False, vid)
+    b = pf.Filter(pf.make_params(1000, 128, 128, dtype, x0=x0, y0=y0, seed=5, stream_id=3, state_only=True))
+    for t in range(1, 5):
+        a.step(fr[t])
+        b.step(fr[t])
+        assert a.estimate() == b.estimate()
+    u, v = a.export(), b.export()
+    assert np.array_equal(u["x"], v["x"]) and np.array_equal(u["y"], v["y"])
+    a.close()
+    b.close()
