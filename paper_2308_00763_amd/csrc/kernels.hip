@@ -2953,12 +2953,15 @@ __global__ __launch_bounds__(kBlock) void gumbel_kernel(StepArgs a)
 // line per lane).  At most 8 slots left instead of 16 measured the same, 32
 // 11 % more, 52 27 % more.
 //
-// Filters of at most kMaskParticles particles first mark, one bit each, the
-// particles that any acceptance word could accept (in a tracking step mostly
-// those of the best pixel cell, one in a hundred), and every workgroup keeps
-// the marks in LDS: a proposal without one is rejected without its gather.
+// First the particles that any acceptance word could accept are marked, one
+// bit each (in a tracking step mostly those of the best pixel cell, one in a
+// hundred): a proposal without a mark is rejected without its gather.  Up to
+// kMaskParticles particles every workgroup keeps the marks in LDS; above, they
+// are read from memory, where those of 2^24 particles (2 MB) fit the L2 of
+// each XCD and the disk terms (64 MB) do not.
 // 2^18 FP32 particles: 130 -> 65 us and 3 for the marks, which is mostly the
-// random words.
+// random words; 2^20 FP16 422 -> 311, and 2^24 25.0 -> 5.9 ms (one trial and
+// one gather at a time: 590 us and 18.8 ms).
 constexpr int kFewSlots = 16;
 constexpr int kMaskParticles = 1 << 19;  // 64 KB of marks
 
@@ -2983,8 +2986,8 @@ __global__ __launch_bounds__(kBlock) void rejection_mask_kernel(StepArgs a)
     if ((threadIdx.x & 63) == 0) static_cast<uint64_t*>(a.q)[j >> 6] = b;
 }
 
-// TB threads; MASK: the marks in dynamic LDS (one 64-bit word per 64 slots).
-template <int DT, int TB, bool MASK>
+// TB threads; LDS: the marks in dynamic LDS (one 64-bit word per 64 slots).
+template <int DT, int TB, bool LDS>
 __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
 {
     using Store = typename ModeT<DT>::Store;
@@ -2996,13 +2999,18 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
     const uint32_t t = blk->t;  // this step's index (the combine has advanced the count)
     const double M = blk->M;
     const int Smax = blk->Smax;
-    if constexpr (MASK) {
+    const auto* q_marks = gbl(static_cast<const uint32_t*>(a.q));
+    if constexpr (LDS) {
         const auto* src = gbl(static_cast<const uint64_t*>(a.q));
         for (int i = threadIdx.x; i < (n + 63) / 64; i += TB) reinterpret_cast<uint64_t*>(s_marks)[i] = src[i];
         __syncthreads();
     }
     auto accepts = [&](int Sc, uint32_t wu) { return rejection_accepts<DT>(a, M, Smax, Sc, wu); };
-    auto marked = [&](int p) { return !MASK || ((s_marks[p >> 5] >> (p & 31)) & 1u) != 0; };
+    auto marked = [&](int p) {
+        uint32_t word;
+        if constexpr (LDS) word = s_marks[p >> 5]; else word = q_marks[p >> 5];
+        return ((word >> (p & 31)) & 1u) != 0;
+    };
     auto words = [&](int slot, int pair) {
         return philox4x32_10((uint32_t)slot, t, a.stream_id, 2u + (uint32_t)pair, a.key0, a.key1);
     };
@@ -3040,38 +3048,24 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
                 p[u + 2] = particle(w.v3);
             }
             c = p[kTrials];
-            if constexpr (MASK) {
-                uint32_t left = 0;  // the marked trials
+            uint32_t left = 0;  // the marked trials
 #pragma unroll
-                for (int u = 0; u < kTrials; ++u) {
-                    if (m + u == cap - 1) c = p[u];  // the last trial's proposal is kept
-                    if (m + u < cap && marked(p[u])) left |= 1u << u;
+            for (int u = 0; u < kTrials; ++u) {  // every word loaded (all proposals are in range)
+                if (m + u == cap - 1) c = p[u];  // the last trial's proposal is kept
+                left |= (uint32_t)((m + u < cap) & marked(p[u])) << u;
+            }
+            while (left && !done) {  // the first of them, mostly the only one
+                const int f = __builtin_ctz(left);
+                left &= left - 1;
+                int pf = p[0];
+                uint32_t wf = wu[0];
+#pragma unroll
+                for (int u = 1; u < kTrials; ++u) {
+                    if (u == f) { pf = p[u]; wf = wu[u]; }
                 }
-                while (left && !done) {  // the first of them, mostly the only one
-                    const int f = __builtin_ctz(left);
-                    left &= left - 1;
-                    int pf = p[0];
-                    uint32_t wf = wu[0];
-#pragma unroll
-                    for (int u = 1; u < kTrials; ++u) {
-                        if (u == f) { pf = p[u]; wf = wu[u]; }
-                    }
-                    if (accepts(S[pf], wf)) {
-                        c = pf;
-                        done = true;
-                    }
-                }
-            } else {
-                int s[kTrials];
-#pragma unroll
-                for (int u = 0; u < kTrials; ++u) s[u] = S[p[u]];
-#pragma unroll
-                for (int u = kTrials - 1; u >= 0; --u) {
-                    if (m + u == cap - 1) c = p[u];
-                    if (m + u < cap && accepts(s[u], wu[u])) {
-                        c = p[u];
-                        done = true;
-                    }
+                if (accepts(S[pf], wf)) {
+                    c = pf;
+                    done = true;
                 }
             }
         }
@@ -3452,17 +3446,18 @@ static hipError_t launch_pass_c_stream(const StepArgs& a, hipStream_t s, const K
 }
 
 // With 64 KB of marks (2^19 particles) two workgroups fit a CU, hence the
-// larger ones past 2^18.
+// larger ones past 2^18; more marks than that would leave one, so they stay in
+// memory.
 template <int DT>
 static hipError_t launch_rejection(const StepArgs& a, hipStream_t s, const KTiming& tm)
 {
     const dim3 g((unsigned)((a.n + kBlock - 1) / kBlock));
-    if (a.n > kMaskParticles) return launch1(rejection_kernel<DT, kBlock, false>, g, dim3(kBlock), s, tm, a);
     KTiming t0, t1;
     t0.start = tm.start;
     t1.stop = tm.stop;
     const hipError_t e = launch1(rejection_mask_kernel<DT>, g, dim3(kBlock), s, t0, a);
     if (e != hipSuccess) return e;
+    if (a.n > kMaskParticles) return launch1(rejection_kernel<DT, kBlock, false>, g, dim3(kBlock), s, t1, a);
     const unsigned lds = (unsigned)((a.n + 63) / 64 * 8);
     if (a.n > kMaskParticles / 2)
         return launch1(rejection_kernel<DT, 1024, true>, dim3((unsigned)((a.n + 1023) / 1024)), dim3(1024), s, t1, a, lds);

@@ -45,7 +45,7 @@ def _check(got, gs, anc, margin):
 
 @pytest.mark.parametrize("n, cap, sigma", [(1, 64, (5.0, 2.0)), (63, 64, (9.0, 9.0)), (65, 128, (9.0, 9.0)),
                                            (300, 192, (9.0, 9.0)), (2049, 16320, (9.0, 9.0)), (4096, 64, (0.0, 0.0)),
-                                           # marks in LDS: the larger workgroups, their largest size, none
+                                           # marks in LDS: the larger workgroups, their largest size; read from memory
                                            (262145, 256, (5.0, 2.0)), (524288, 128, (5.0, 2.0)),
                                            (524289, 128, (5.0, 2.0))])
 def test_rejection_groups(n, cap, sigma):
