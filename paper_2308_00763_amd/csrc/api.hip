@@ -37,6 +37,7 @@ struct pf_filter {
     // per-pass timing (pf_profile_start / pf_profile_read)
     std::vector<hipEvent_t> prof_ev;  // kProfEv events per recorded step
     uint32_t prof_max, prof_used;
+    StreamRule rule;  // its part in whether pass A streams
 };
 
 // A batch of filters in one workspace:
@@ -81,6 +82,7 @@ struct pf_batch {
     size_t stage_bytes;
     std::vector<uint8_t> map_active;  // stepped set of the uploaded tile map
     bool map_valid;
+    bool map_stream;                  // whether its pass A streams
     bool poisoned;
 };
 
@@ -440,6 +442,10 @@ void setup_filter(pf_filter* h, const pf_params& pr, uint8_t* ws, hipStream_t st
                     !a.naive_half && !a.mh_steps && !a.rj_cap && !a.gumbel
                 ? 1
                 : 0;
+    const double fall = 2.0 * (p->fg - p->bg) * (p->fg - p->bg) * (p->lik_norm == PF_LIK_MEAN ? 1 : a.nd) / p->kappa;
+    h->rule = stream_rule(p->dtype == PF_F32, p->dtype == PF_F64, a.dg_s != nullptr, p->disk_radius, fall, p->sigma_x,
+                          p->sigma_y);
+    a.stream_tiles = a.naive_lik || a.naive_half ? INT32_MAX : h->rule.tiles;
     a.px2 = a.gather ? at(h, L.px2) : nullptr;
     a.py2 = a.gather ? at(h, L.py2) : nullptr;
     a.q2 = a.gather ? at(h, L.q2) : nullptr;
@@ -1217,6 +1223,16 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
             if (b->ta[ent[i].fid] == kSizesA[c]) a_count[c] += h->L.ntiles;
     }
     const int sizes_used = (a_count[0] > 0) + (a_count[1] > 0) + (a_count[2] > 0);
+    // members of the default size stream if that pays for them together
+    bool stream = same && b->map_stream;
+    if (!same && b->dtype != PF_F64 && a_count[1] >= kStreamTiles) {
+        StreamSum sum;
+        for (int32_t i = 0; i < ne; ++i) {
+            const pf_filter* h = b->f[ent[i].fid];
+            if (b->ta[ent[i].fid] == 256) sum.add(h->rule, h->L.ntiles);
+        }
+        stream = sum.streams();
+    }
     int32_t a_begin[3] = {0, a_count[0], a_count[0] + a_count[1]};
     if (sizes_used > 1 && !same) {
         int32_t fillp[3] = {a_begin[0], a_begin[1], a_begin[2]};
@@ -1245,6 +1261,7 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
     ba.a_tiles = nullptr;
     ba.entry0 = 0;
     ba.tiles = tiles;
+    ba.stream = stream ? 1 : 0;
     ba.seen = nullptr;
     ba.step_no = 0;
     if (!capturing) {
@@ -1290,6 +1307,7 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
         b->map_active.resize((size_t)n);
         for (int32_t k = 0; k < n; ++k) b->map_active[k] = (uint8_t)(active ? active[k] != 0 : 1);
         b->map_valid = true;
+        b->map_stream = stream;
     }
     for (int32_t i = 0; i < ne; ++i) b->f[ent[i].fid]->t = ent[i].t;
     return ok();

@@ -1109,14 +1109,9 @@ __global__ __launch_bounds__(kTile / PPT) void pass_a_kernel(StepArgs a)
 // last, alone on its CU, after 62; 2^24 particles 60 -> 52 us, the batch 205 ->
 // 182.  More, shorter workgroups instead (two rounds of them) gave half of that.
 //
-// The line lies at 4096 tiles, about three per workgroup: below, the first
-// tile's table costs what the later ones gain (FP16 us of pass A one-tile |
-// streaming: 2^21 r = 5 11.9 | 16.5, 3 2^20 15.5 | 18.4, 2^22 19.0 | 19.8, 2^22 r = 8
-// 24.3 | 21.4, 2^23 33.9 | 28.6).  The double mode does not stream: it is bound by
-// memory, and its one-tile pass needs half the registers (2^23 + 1 particles: 158
-// us a step against 165).
-constexpr int kStreamTiles = 4096;
-constexpr int kCells = 2048;      // cells of the table
+// Which filters and batches stream: stream_rule.hpp.  The double mode does not:
+// it is bound by memory, and its one-tile pass needs half the registers (2^23 + 1
+// particles: 158 us a step against 165).
 constexpr int kMaxTableBuilds = 6;  // per run; then every tile takes its sums from the row prefixes
 
 struct PassAStreamLds {
@@ -1299,6 +1294,7 @@ __device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const u
             c.W = aq->W; c.H = aq->H; c.r = aq->r; c.nd = aq->nd; c.fg = aq->fg; c.bg = aq->bg;
             c.beta = aq->beta;
             const int r = RC > 0 ? RC : c.r;
+            const bool later = t + 1 < t1;  // the table is for later tiles too
             if (tile_max == INT32_MAX) {
                 // Cells are clamped where that changes none of the disk's pixels.
                 const int lox = -(r - 1) - cnx, hix = c.W - 1 + (r - 1) - cnx;
@@ -1349,7 +1345,7 @@ __device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const u
                 };
                 bool table = false;
                 if (builds < kMaxTableBuilds) {
-                    const int m = t + 1 < t1 ? 2 : 0;
+                    const int m = later ? 2 : 0;
                     table = bw > 0 && frame_box(m, true);
                     for (int k = m; !table && k >= 0; --k) table = frame_box(k, false);
                 }
@@ -1417,7 +1413,7 @@ __device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const u
 #pragma unroll
             for (int i = 0; i < PPT; ++i) w[i] = k0 + i < n ? weight_of(S[i], tile_max, c.beta) : (float)0;
             publish(w, tile_max);
-            if (bw > 0 && tile_max > ref) {
+            if (later && bw > 0 && tile_max > ref) {
                 // the table's weights, relative to the largest maximum so far
                 // (which later tiles most likely reach too)
                 ref = tile_max;
@@ -3400,7 +3396,7 @@ static hipError_t launch_pass_a_t(const StepArgs& a, hipStream_t s, const KTimin
     }
     }
     if constexpr (DT != PF_F64) {
-        if (a.ntiles >= kStreamTiles && !a.naive_lik && !a.naive_half)
+        if (a.ntiles >= a.stream_tiles)
             return a.wt ? launch_pass_a_stream<DT, true>(a, s, tm) : launch_pass_a_stream<DT, false>(a, s, tm);
     }
     if constexpr (DT != PF_F64) {
@@ -3556,7 +3552,7 @@ static hipError_t launch_batch_pass_a_p(int rc, const BatchArgs& b, int tiles, h
 {
     const dim3 g((unsigned)tiles), blk(kTile / PPT);
     if constexpr (DT != PF_F64 && PPT == kPPT) {
-        if (tiles >= kStreamTiles) {
+        if (b.stream) {
             BatchArgs bb = b;
             bb.tiles = tiles;
             if (rc == 5) return launch_batch_stream<DT, 5>(bb, s, tm);

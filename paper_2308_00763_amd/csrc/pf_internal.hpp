@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/pf.h"
+#include "stream_rule.hpp"
 
 namespace pf {
 
@@ -25,8 +26,6 @@ constexpr int kBlockA = kTile / kPPT;  // threads per pass-A workgroup
 constexpr int kWavesA = kBlockA / 64;
 constexpr int kPrefPitch = 134;    // LDS row-prefix table: u16 entries per window row (67 dwords)
 constexpr int kPrefBase = 3;       // entry of P[0] in a row (so P[4l+1..4l+4] is 4-byte aligned)
-constexpr int kPrefRows = 64;      // LDS row-prefix table: window rows
-constexpr int kWinMaxW = 128;      // widest frame window staged in LDS
 constexpr int kMaxRadius = 32;
 
 // Combine configuration of a filter of nt tiles: class 0 = one wave of 64
@@ -256,6 +255,7 @@ struct StepArgs {
     // combine writes the tiles' end slots to ecol as well and sets pend.
     int32_t gather;
     int32_t one;        // a single filter of one tile at the default sizes, systematic: its step is one launch
+    int32_t stream_tiles;  // tiles from which the filter's pass A streams (INT32_MAX: never)
     void* px2;
     void* py2;
     void* q2;
@@ -286,6 +286,7 @@ struct BatchArgs {
     int32_t entry0;     // combine: entry of the launch's first workgroup;
                         // listed pass A: index in a_tiles of its first tile
     int32_t tiles;      // streaming passes: the launch's tiles (set by the launcher)
+    int32_t stream;     // pass A of the default size streams
     uint32_t step_no;   // pass C stores it in *seen (pinned host memory; may be null)
     uint32_t* seen;
 };

@@ -1,0 +1,90 @@
+"""The rule by which pass A streams (stream_rule.hpp) against measured times of
+both passes: it takes the faster one wherever they differ by 4 % or more."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+SHIM = r'''
+#include "stream_rule.hpp"
+extern "C" int single(int f32, int f64, int diag, int r, double fall, double sx, double sy) {
+    return pf::stream_rule(f32, f64, diag, r, fall, sx, sy).tiles;
+}
+extern "C" int batch(int f32, int n, const int* radii, const double* sx, const double* sy, const int* tiles, double fall) {
+    pf::StreamSum s;
+    for (int i = 0; i < n; ++i) s.add(pf::stream_rule(f32, 0, 0, radii[i], fall, sx[i], sy[i]), tiles[i]);
+    return s.streams();
+}
+'''
+FALL = 2 * 128 ** 2 / 50.0  # the contrast of a 228 on 100 disk under kappa = 50
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rule")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "shim.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC",
+                    "-I", os.path.join(ROOT, "paper_2308_00763_amd", "csrc"), str(d / "shim.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.single.argtypes = [ctypes.c_int] * 4 + [ctypes.c_double] * 3
+    return lib
+
+
+M = 1 << 20
+
+
+@pytest.mark.parametrize("f32, r, sigma, n, one, streaming", [
+    # us a step, 512 x 512 frames; f32 = 0: FP16
+    (0, 5, (10.0, 8.0), 6 * M, 168.9, 223.3), (0, 5, (10.0, 8.0), 16 * M, 334.9, 436.8),
+    (0, 5, (7.0, 5.0), 16 * M, 114.5, 148.5), (0, 5, (6.0, 5.0), 8 * M, 67.5, 78.7),
+    (0, 3, (20.0, 9.0), 16 * M, 436.6, 462.1), (0, 3, (5.0, 2.0), 6 * M, 55.4, 51.8),
+    (0, 3, (5.0, 4.0), 4 * M, 43.6, 48.0), (0, 3, (6.0, 6.0), 16 * M, 120.2, 154.3),
+    (0, 5, (5.0, 2.0), 16 * M, 110.3, 94.6), (0, 5, (5.0, 2.0), 6 * M, 53.1, 50.7),
+    (0, 5, (1.0, 1.0), 5 * M, 45.0, 41.8), (0, 5, (5.0, 4.0), 4 * M, 42.2, 44.9),
+    (0, 8, (5.0, 2.0), 4 * M, 47.1, 44.7), (0, 8, (5.0, 2.0), 16 * M, 130.0, 97.6),
+    (0, 8, (10.0, 8.0), 16 * M, 2391.9, 2657.6), (0, 8, (7.0, 5.0), 16 * M, 143.8, 166.8),
+    (0, 8, (5.0, 5.0), 16 * M, 135.6, 119.7), (0, 8, (7.0, 7.0), 6 * M, 355.4, 450.8),
+    (0, 12, (5.0, 2.0), 6 * M, 77.1, 64.4), (0, 12, (5.0, 4.0), 4 * M, 60.0, 66.1),
+    (0, 12, (6.0, 6.0), 16 * M, 1827.0, 2458.9), (0, 16, (5.0, 2.0), 4 * M, 69.0, 62.0),
+    (0, 16, (2.0, 6.0), 4 * M, 5630.0, 4360.0), (0, 16, (5.0, 5.0), 4 * M, 1520.0, 2158.0),
+    (0, 20, (5.0, 5.0), 4 * M, 6925.0, 5330.0),
+    (1, 5, (10.0, 8.0), 16 * M, 385.5, 477.6), (1, 5, (5.0, 2.0), 16 * M, 159.4, 148.6),
+    (1, 3, (7.0, 5.0), 6 * M, 61.8, 80.4), (1, 12, (5.0, 2.0), 16 * M, 210.1, 158.9),
+    (1, 8, (5.0, 2.0), 6 * M, 67.3, 62.1), (1, 8, (6.0, 5.0), 16 * M, 180.8, 195.6)])
+def test_single_filters_take_the_faster_pass(rule, f32, r, sigma, n, one, streaming):
+    assert abs(one - streaming) > 0.04 * min(one, streaming)
+    assert (n // 1024 >= rule.single(f32, 0, 0, r, FALL, *sigma)) == (streaming < one)
+
+
+@pytest.mark.parametrize("f32, radii, sigma, fall, members, tiles, one, streaming", [
+    (0, (5,), (5.0, 2.0), FALL, 8192, 1, 81.9, 95.3), (0, (5,), (5.0, 2.0), FALL, 16384, 1, 149.8, 188.3),
+    (0, (5,), (5.0, 2.0), FALL, 4096, 2, 78.0, 82.6), (0, (5,), (5.0, 2.0), FALL, 1024, 8, 73.2, 68.9),
+    (0, (5,), (5.0, 2.0), FALL, 8192, 4, 273.3, 244.6), (0, (5,), (5.0, 2.0), FALL, 512, 64, 250.5, 198.4),
+    (0, (8,), (5.0, 2.0), FALL, 16384, 2, 319.7, 344.0), (0, (8,), (5.0, 2.0), FALL, 1024, 4, 51.6, 56.3),
+    (0, (12,), (5.0, 2.0), FALL, 16384, 1, 211.6, 237.2), (0, (12,), (5.0, 2.0), FALL, 8192, 2, 194.4, 176.9),
+    (0, (3, 12, 5), (5.0, 2.0), FALL, 8190, 1, 96.8, 109.1), (0, (3, 12, 5), (5.0, 2.0), FALL, 510, 64, 285.0, 205.2),
+    (0, (3, 8, 12), (5.0, 2.0), 0.33, 126, 64, 1816.0, 2408.0),
+    (1, (5,), (5.0, 2.0), FALL, 8192, 1, 91.2, 111.0), (1, (8,), (5.0, 2.0), FALL, 1024, 4, 55.8, 61.6)])
+def test_batches_take_the_faster_pass(rule, f32, radii, sigma, fall, members, tiles, one, streaming):
+    rs = [radii[i % len(radii)] for i in range(members)]
+    arr = lambda t, v: (t * members)(*v)
+    got = rule.batch(f32, members, arr(ctypes.c_int, rs), arr(ctypes.c_double, [sigma[0]] * members),
+                     arr(ctypes.c_double, [sigma[1]] * members), arr(ctypes.c_int, [tiles] * members),
+                     ctypes.c_double(fall))
+    assert bool(got) == (streaming < one)
+
+
+def test_what_never_streams(rule):
+    never = 2 ** 31 - 1
+    assert rule.single(0, 1, 0, 5, FALL, 5.0, 2.0) == never          # FP64
+    assert rule.single(1, 0, 1, 5, FALL, 5.0, 2.0) == never          # FP32 with diagnostics
+    assert rule.single(0, 0, 0, 5, 0.0, 5.0, 2.0) == never           # no contrast: the cloud spreads
+    assert rule.single(0, 0, 0, 5, 1e-3, 5.0, 2.0) == never
+    for sigma in ((0.0, 0.0), (1e6, 1e6), (0.0, 1e6)):
+        for r in (1, 5, 8, 32):
+            t = rule.single(0, 0, 0, r, FALL, *sigma)
+            assert 4096 <= t <= never
