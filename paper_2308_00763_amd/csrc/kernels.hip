@@ -3351,6 +3351,13 @@ static int resident_cap(K kernel, int threads)
     return occ * cus;
 }
 
+// Whether radius 8 streams with its rows unrolled.  FP32 without write-through
+// stores (above kWtMaxTiles, and batches) has no registers left for that: the
+// loop over the tiles spills (3 2^22 particles 117 us a step, with the run-time
+// radius 104; written through, 2^23, 76 and 79).
+template <int DT, bool WT>
+constexpr bool kStreamR8 = DT != PF_F32 || WT;
+
 template <int DT, int RC, bool WT>
 static hipError_t launch_pass_a_stream_r(const StepArgs& a, hipStream_t s, const KTiming& tm)
 {
@@ -3362,7 +3369,9 @@ template <int DT, bool WT>
 static hipError_t launch_pass_a_stream(const StepArgs& a, hipStream_t s, const KTiming& tm)
 {
     if (a.r == 5) return launch_pass_a_stream_r<DT, 5, WT>(a, s, tm);
-    if (a.r == 8) return launch_pass_a_stream_r<DT, 8, WT>(a, s, tm);
+    if constexpr (kStreamR8<DT, WT>) {
+        if (a.r == 8) return launch_pass_a_stream_r<DT, 8, WT>(a, s, tm);
+    }
     return launch_pass_a_stream_r<DT, 0, WT>(a, s, tm);
 }
 
@@ -3556,7 +3565,9 @@ static hipError_t launch_batch_pass_a_p(int rc, const BatchArgs& b, int tiles, h
             BatchArgs bb = b;
             bb.tiles = tiles;
             if (rc == 5) return launch_batch_stream<DT, 5>(bb, s, tm);
-            if (rc == 8) return launch_batch_stream<DT, 8>(bb, s, tm);
+            if constexpr (kStreamR8<DT, false>) {
+                if (rc == 8) return launch_batch_stream<DT, 8>(bb, s, tm);
+            }
             return launch_batch_stream<DT, 0>(bb, s, tm);
         }
     }

@@ -23,6 +23,7 @@ M = 1 << 20
     ("f16", 5, 256, (128, 128), (5.0, 2.0), "outliers", None, 6 * M + 777),
     ("f32", 8, 256, (128, 128), (3.0, 3.0), "two_places", None, 5 * M + 777),
     ("bf16", 5, 256, (128, 128), (5.0, 2.0), "spread", None, 6 * M + 777),
+    ("f32", 8, 256, (128, 128), (5.0, 2.0), "outliers", None, 8193 * 1024 - 5),  # FP32 past the write-through sizes
     ("f16", 5, 256, (128, 128), (5.0, 2.0), None, None, 8193 * 1024 - 5),
 ])
 def test_stream_equals_one_tile_pass(dtype, r, side, start, sigma, kind, pitch, n):
@@ -37,6 +38,7 @@ def test_stream_equals_one_tile_pass(dtype, r, side, start, sigma, kind, pitch, 
 @pytest.mark.parametrize("dtype, radii, sizes", [
     ("f16", (5,), [1, 1024, 1025, 70001, 204800] * 45),    # streams: a run's last tile, runs of one tile
     ("bf16", (8,), [1, 1024, 1025, 70001, 204800] * 45),
+    ("f32", (8,), [1, 1024, 1025, 70001, 204800] * 45),
     ("f32", (3, 12, 5), [1, 1024, 1025, 70001, 204800] * 45),
     ("f16", (5, 12), [1000] * 4100),                       # enough tiles, one each: does not stream
 ])
