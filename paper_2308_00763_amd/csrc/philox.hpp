@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "exp64.hpp"
+
 namespace pf {
 
 struct u32x4 {
@@ -75,34 +77,6 @@ __device__ __forceinline__ double uniform53_times_2_32(uint32_t hi, uint32_t lo)
 // Polynomial coefficients: the functions' own Taylor series economised at
 // Chebyshev nodes in 60 digits; what they leave out is below 2e-17 of the
 // result.
-
-// A constant in scalar registers, formed where it is used: left to itself the
-// compiler keeps a loop's double constants in vector registers (40 of them).
-__device__ __forceinline__ double coef(double c)
-{
-    __asm__ volatile("" : "+s"(c));
-    return c;
-}
-
-// exp(d) for d <= 0, the weights: d = k ln 2 + r, |r| <= ln 2 / 2, exp(r) = 1 + r
-// + r^2 P(r) (21 instructions against the library's 42).
-__device__ __forceinline__ double exp_nonpos(double d)
-{
-    d = d < -800.0 ? -800.0 : d;  // rounds to 0 from there on; a NaN stays
-    const double k = __builtin_rint(d * coef(0x1.71547652b82fep+0));
-    const double r = __builtin_fma(k, -coef(0x1.a39ef35793c76p-33), __builtin_fma(k, -coef(0x1.62e42feep-1), d));
-    double p = coef(0x1.af38a0d2d9620p-26);
-    p = __builtin_fma(p, r, coef(0x1.28917e2c43a66p-22));
-    p = __builtin_fma(p, r, coef(0x1.71de0db21e27fp-19));
-    p = __builtin_fma(p, r, coef(0x1.a019b9133a48ap-16));
-    p = __builtin_fma(p, r, coef(0x1.a01a01a7c327ap-13));
-    p = __builtin_fma(p, r, coef(0x1.6c16c1788a49bp-10));
-    p = __builtin_fma(p, r, coef(0x1.11111111109b4p-7));
-    p = __builtin_fma(p, r, coef(0x1.5555555553d67p-5));
-    p = __builtin_fma(p, r, coef(0x1.5555555555556p-3));
-    p = __builtin_fma(p, r, 0.5);
-    return __builtin_ldexp(1.0 + __builtin_fma(r * r, p, r), (int)k);
-}
 
 // -2 ln(a) for a in [2^-53, 1].  a = 2^e m with m in [sqrt(1/2), sqrt(2)), f =
 // m - 1, s = f / (2 + f): ln m = 2 atanh(s) = f - h + s (h + R) with h = f^2 / 2
