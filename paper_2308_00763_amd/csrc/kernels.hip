@@ -2809,13 +2809,19 @@ __global__ __launch_bounds__(TPB) void resample_naive_kernel(StepArgs a)
 // are the integer disk terms S of pass A over the likelihood's denominator:
 // L = S / denom in double in the FP64 mode; the reduced modes compare
 // exp2((S_i - S_k) beta) in float.  Proposals gather S from global memory.
-// The proposals do not depend on the chain, only the acceptances do, so
-// kTrials of them are drawn and gathered at a time: a chain waits for memory
-// once for eight steps, not once for each.
+// The proposals do not depend on the chain, only the acceptances do.  Up to
+// kLatencyParticles particles (GROUPS) kTrials of them are drawn and gathered
+// at a time: a chain waits for memory once for eight steps, not once for each
+// (2^14 FP16 particles, 32 steps: 21.0 -> 17.4 us a step; 2^16 22.2 -> 20.3).  Above,
+// the gathers' throughput is the bound, and what counts is the waves in flight
+// (the groups' registers leave six per SIMD) and that none is made for
+// nothing: a pair of steps at a time, which share a random block (2^20, 4 steps
+// 59 us, in groups 81; 2^22, 1 step 172 and 567).
 
 constexpr int kTrials = 8;
+constexpr int kLatencyParticles = 1 << 16;  // Metropolis: up to here at most one wave per SIMD
 
-template <int DT>
+template <int DT, bool GROUPS>
 __global__ __launch_bounds__(kBlock) void metropolis_kernel(StepArgs a)
 {
     using Store = typename ModeT<DT>::Store;
@@ -2827,36 +2833,79 @@ __global__ __launch_bounds__(kBlock) void metropolis_kernel(StepArgs a)
     int k = j;
     int Sk = S[k];
     double Lk = (double)Sk / a.denom;
-    for (int b0 = 0; b0 < a.mh_steps; b0 += kTrials) {
-        int idx[kTrials], Si[kTrials];
-        uint32_t wu[kTrials];
-#pragma unroll
-        for (int u = 0; u < kTrials; u += 2) {
-            const u32x4 w = philox4x32_10((uint32_t)j, t, a.stream_id, 2u + (uint32_t)((b0 + u) >> 1), a.key0, a.key1);
-            idx[u] = (int)__umulhi(w.v0, (uint32_t)n);
-            idx[u + 1] = (int)__umulhi(w.v2, (uint32_t)n);
-            wu[u] = w.v1;
-            wu[u + 1] = w.v3;
-        }
-#pragma unroll
-        for (int u = 0; u < kTrials; ++u) Si[u] = S[idx[u]];
-#pragma unroll
-        for (int u = 0; u < kTrials; ++u) {
-            if (b0 + u >= a.mh_steps) break;  // uniform
-            if constexpr (DT == PF_F64) {
-                const double Li = (double)Si[u] / a.denom;
-                if (Li >= Lk || ((double)wu[u] + 0.5) * 0x1.0p-32 <= exp(Li - Lk)) {
-                    k = idx[u];
-                    Lk = Li;
-                }
-            } else {
-                if (Si[u] >= Sk || ((float)(wu[u] >> 8) + 0.5f) * 0x1.0p-24f <=
-                                       __builtin_amdgcn_exp2f((float)(Si[u] - Sk) * a.beta)) {
-                    k = idx[u];
-                    Sk = Si[u];
-                }
+    const int steps = a.mh_steps;
+    auto words = [&](int b) {
+        return philox4x32_10((uint32_t)j, t, a.stream_id, 2u + (uint32_t)(b >> 1), a.key0, a.key1);
+    };
+    auto test = [&](int i, int Si, uint32_t wu) {
+        if constexpr (DT == PF_F64) {
+            const double Li = (double)Si / a.denom;
+            if (Li >= Lk || ((double)wu + 0.5) * 0x1.0p-32 <= exp(Li - Lk)) {
+                k = i;
+                Lk = Li;
+            }
+        } else {
+            if (Si >= Sk ||
+                ((float)(wu >> 8) + 0.5f) * 0x1.0p-24f <= __builtin_amdgcn_exp2f((float)(Si - Sk) * a.beta)) {
+                k = i;
+                Sk = Si;
             }
         }
+    };
+    int b = 0;
+    if constexpr (GROUPS) {
+        struct Group {
+            int idx[kTrials], S[kTrials];
+            uint32_t wu[kTrials];
+        };
+        auto draw = [&](Group& g, int b0) {
+#pragma unroll
+            for (int u = 0; u < kTrials; u += 2) {
+                const u32x4 w = words(b0 + u);
+                g.idx[u] = (int)__umulhi(w.v0, (uint32_t)n);
+                g.idx[u + 1] = (int)__umulhi(w.v2, (uint32_t)n);
+                g.wu[u] = w.v1;
+                g.wu[u + 1] = w.v3;
+            }
+#pragma unroll
+            for (int u = 0; u < kTrials; ++u) g.S[u] = S[g.idx[u]];
+        };
+        auto tests = [&](const Group& g, int count) {
+#pragma unroll
+            for (int u = 0; u < kTrials; ++u)
+                if (u < count) test(g.idx[u], g.S[u], g.wu[u]);
+        };
+        const int whole = steps & ~(kTrials - 1);
+        Group g;
+        if constexpr (DT == PF_F64) {
+            for (; b < whole; b += kTrials) {
+                draw(g, b);
+                tests(g, kTrials);
+            }
+        } else if (whole) {  // the next group's gathers are in flight during the tests
+            draw(g, 0);
+            for (; b + kTrials < whole; b += kTrials) {
+                Group nx;
+                draw(nx, b + kTrials);
+                tests(g, kTrials);
+                g = nx;
+            }
+            tests(g, kTrials);
+            b = whole;
+        }
+        if (steps - b > kTrials / 2) {
+            draw(g, b);
+            tests(g, steps - b);
+            b = steps;
+        }
+    }
+    for (; b < steps; b += 2) {  // a pair of steps at a time
+        const u32x4 w = words(b);
+        const bool two = b + 1 < steps;  // uniform
+        const int i0 = (int)__umulhi(w.v0, (uint32_t)n), i1 = (int)__umulhi(w.v2, (uint32_t)n);
+        const int s0 = S[i0], s1 = two ? S[i1] : 0;
+        test(i0, s0, w.v1);
+        if (two) test(i1, s1, w.v3);
     }
     static_cast<Store*>(a.sx)[j] = static_cast<const Store*>(a.px)[k];
     static_cast<Store*>(a.sy)[j] = static_cast<const Store*>(a.py)[k];
@@ -3473,8 +3522,11 @@ template <int DT>
 static hipError_t launch_pass_c_t(const StepArgs& a, hipStream_t s, const KTiming& tm)
 {
     const dim3 g((unsigned)a.ntiles);
-    if (a.mh_steps > 0)
-        return launch1(metropolis_kernel<DT>, dim3((unsigned)((a.n + kBlock - 1) / kBlock)), dim3(kBlock), s, tm, a);
+    if (a.mh_steps > 0) {
+        const dim3 gm((unsigned)((a.n + kBlock - 1) / kBlock));
+        if (a.n <= kLatencyParticles) return launch1(metropolis_kernel<DT, true>, gm, dim3(kBlock), s, tm, a);
+        return launch1(metropolis_kernel<DT, false>, gm, dim3(kBlock), s, tm, a);
+    }
     if (a.rj_cap > 0) return launch_rejection<DT>(a, s, tm);
     if (a.gumbel)
         return launch1(gumbel_kernel<DT>, dim3((unsigned)((a.n + kBlock - 1) / kBlock)), dim3(kBlock), s, tm, a);
