@@ -3007,8 +3007,18 @@ __global__ __launch_bounds__(kBlock) void gumbel_kernel(StepArgs a)
 // 2^18 FP32 particles: 130 -> 65 us and 3 for the marks, which is mostly the
 // random words; 2^20 FP16 422 -> 311, and 2^24 25.0 -> 5.9 ms (one trial and
 // one gather at a time: 590 us and 18.8 ms).
+//
+// Under a broad likelihood nearly every particle is marked and a slot needs few
+// trials: the marks and the trials drawn ahead are then work for nothing.  So
+// from a chance of kLikely per trial on the slots go on one trial at a time,
+// without marks, and in the larger filters, from a chance of a few in a
+// hundred on, so do the waves that find more than half of their proposals
+// marked (FP32, us a step one at a time | ahead | this rule: 2^20 chance 0.29 100
+// | 146 | 93, 0.06 171 | 368 | 181; 2^18 chance 0.97 44 | 50 | 44).
 constexpr int kFewSlots = 16;
 constexpr int kMaskParticles = 1 << 19;  // 64 KB of marks
+constexpr float kLikely = 0.1f;
+constexpr int kEarlyMarks = 1 << 16;  // particles whose marks are copied before they are known to be wanted
 
 // Acceptance of a proposal of disk term Sc with acceptance word wu (monotone
 // in wu: what wu = 0 rejects, every word rejects).
@@ -3021,10 +3031,20 @@ __device__ __forceinline__ bool rejection_accepts(const StepArgs& a, double M, i
         return ((float)(wu >> 8) + 0.5f) * 0x1.0p-24f <= __builtin_amdgcn_exp2f((float)(Sc - Smax) * a.beta);
 }
 
-// The marks go where the prefix sums were (the combine was their last reader).
+// Whether the chance of a trial, the mean weight relative to the maximum, is at
+// least p (NaN: yes).
+template <int DT>
+__device__ __forceinline__ bool rejection_chance(const StepArgs& a, float p)
+{
+    if constexpr (DT == PF_F64) return !(a.blk->Z < (double)p * (double)a.n);
+    else return !(a.blk->Zf < p * (float)a.n);
+}
+
+// The marks go where the prefix sums were (nothing reads them).
 template <int DT>
 __global__ __launch_bounds__(kBlock) void rejection_mask_kernel(StepArgs a)
 {
+    if (a.n > kMaskParticles && rejection_chance<DT>(a, kLikely)) return;  // they will not be read
     const int j = blockIdx.x * kBlock + threadIdx.x;
     const bool mark = j < (int)a.n && rejection_accepts<DT>(a, a.blk->M, a.blk->Smax, a.s_all[min(j, (int)a.n - 1)], 0u);
     const uint64_t b = __ballot(mark);
@@ -3045,11 +3065,16 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
     const double M = blk->M;
     const int Smax = blk->Smax;
     const auto* q_marks = gbl(static_cast<const uint32_t*>(a.q));
-    if constexpr (LDS) {
+    // Few marks are copied to LDS at once, while the first trials' loads are in
+    // flight; more, when they are known to be wanted.
+    const bool early = LDS && TB == kBlock && n <= kEarlyMarks;  // uniform
+    constexpr bool crowds = !LDS || (TB > kBlock && DT != PF_F64);
+    auto copy_marks = [&]() {
         const auto* src = gbl(static_cast<const uint64_t*>(a.q));
         for (int i = threadIdx.x; i < (n + 63) / 64; i += TB) reinterpret_cast<uint64_t*>(s_marks)[i] = src[i];
-        __syncthreads();
-    }
+        if (!early) __syncthreads();
+    };
+    if (early) copy_marks();
     auto accepts = [&](int Sc, uint32_t wu) { return rejection_accepts<DT>(a, M, Smax, Sc, wu); };
     auto marked = [&](int p) {
         uint32_t word;
@@ -3079,7 +3104,33 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
             }
         }
     }
+    // Two trials, the second's gather when the first has failed.
+    auto in_turn = [&]() {
+        while (m < cap && __any(!done)) {
+            if (!done) {
+                const u32x4 w = words(j, m >> 1);
+                if (accepts(S[c], w.v0)) {
+                    done = true;
+                } else {
+                    c = particle(w.v1);
+                    if (accepts(S[c], w.v2)) done = true;
+                    else if (m + 2 < cap) c = particle(w.v3);
+                }
+            }
+            m += 2;
+        }
+        m = cap;
+    };
+    if (rejection_chance<DT>(a, kLikely)) {  // the same for all
+        in_turn();
+    } else if (LDS && !early) {
+        copy_marks();
+    }
+    if (early) __syncthreads();
+    const float crowd_chance = LDS || (DT == PF_F64 && n < 2 * kMaskParticles) ? 0.05f : 0.02f;
+    const bool may_crowd = crowds && rejection_chance<DT>(a, crowd_chance);
     while (m < cap && __popcll(__ballot(!done)) > kFewSlots) {  // the same for the wave
+        bool crowded = false;
         if (!done) {
             int p[kTrials + 1];
             uint32_t wu[kTrials];
@@ -3099,6 +3150,7 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
                 if (m + u == cap - 1) c = p[u];  // the last trial's proposal is kept
                 left |= (uint32_t)((m + u < cap) & marked(p[u])) << u;
             }
+            if (may_crowd) crowded = __popc(left) > kTrials / 2;
             while (left && !done) {  // the first of them, mostly the only one
                 const int f = __builtin_ctz(left);
                 left &= left - 1;
@@ -3115,6 +3167,8 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
             }
         }
         m += kTrials;
+        // marks that keep little from being gathered cost more than that
+        if (may_crowd && __popcll(__ballot(crowded)) > kFewSlots / 2) in_turn();
     }
     for (uint64_t left = m < cap ? __ballot(!done) : 0; left; left &= left - 1) {
         const int src = __builtin_ctzll(left);

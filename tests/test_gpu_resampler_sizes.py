@@ -1,6 +1,8 @@
-"""Metropolis resampling on both sides of the size at which its kernel changes
-(steps in groups of eight, or a pair at a time), and behind the streaming pass
-A.
+"""Metropolis and rejection resampling on both sides of the sizes and the
+likelihoods at which their kernels change: Metropolis in groups of eight or a
+pair of steps at a time, rejection with its marks in LDS (two workgroup sizes)
+or in memory, with trials ahead or one at a time by the chance of a trial, and
+both behind the streaming pass A.
 
 The oracle runs on the GPU's own integer disk terms, so every step is checked
 whatever the pixel ties.  A slot may differ only where one of its tests lies
@@ -54,7 +56,21 @@ def test_metropolis(dtype, n, B):
         _check(dtype, got, gs, anc, margin)
 
 
-@pytest.mark.parametrize("dtype, kw", [("bf16", dict(metropolis_steps=3)), ("f32", dict(metropolis_steps=9))])
+@pytest.mark.parametrize("dtype, n, cap, kappa", [
+    # chance of a trial about 0.01 (kappa 50), 0.025 (3000), 0.06 (6000), 0.3 (20000), nearly 1 (1e6)
+    ("f32", 700, 64, 20000.0), ("f64", 65536, 64, 6000.0), ("f16", 65537, 64, 20000.0), ("f32", 65537, 64, 50.0),
+    ("f32", 262145, 128, 50.0), ("f16", 262145, 64, 6000.0), ("f64", 262145, 64, 6000.0), ("bf16", 262145, 64, 1e6),
+    ("f32", 524288, 64, 20000.0), ("f16", 524289, 128, 50.0), ("f32", 524289, 64, 3000.0), ("f64", 524289, 64, 6000.0),
+    ("f16", 524289, 64, 1e6), ("f16", 1048577, 64, 3000.0)])
+def test_rejection(dtype, n, cap, kappa):
+    for t, got, gs, L in _steps(dtype, n, kappa, rejection_trials=cap):
+        anc, margin, trials = oracle.rejection(L, cap, 11, 3, t)
+        print(f"[sizes] trials {trials.min()}..{trials.max()} mean {trials.mean():.2f}", flush=True)
+        _check(dtype, got, gs, anc, margin)
+
+
+@pytest.mark.parametrize("dtype, kw", [("f16", dict(rejection_trials=64)), ("f32", dict(rejection_trials=64)),
+                                       ("bf16", dict(metropolis_steps=3)), ("f32", dict(metropolis_steps=9))])
 def test_behind_the_streaming_pass(dtype, kw):
     """Against the one-tile pass A (which a filter with the per-pixel likelihood
     takes), bit for bit."""
