@@ -736,7 +736,9 @@ static int export_positions(pf_filter* h, size_t off_x, size_t off_y, double* x,
             void* to = dt == PF_F64 ? (void*)dst[c] : (void*)(buf.get() + (size_t)(c - c0) * bytes);
             e = hipMemcpyAsync(to, at(h, offs[c]), bytes, hipMemcpyDeviceToHost, h->stream);
         }
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+        // also after a failed copy: the one before it may still be under way
+        const hipError_t es = hipStreamSynchronize(h->stream);
+        if (e == hipSuccess) e = es;
         if (e != hipSuccess) return hip_fail(h, e, "export");
         for (int c = c0; c < c1 && dt != PF_F64; ++c) {
             const uint8_t* src = buf.get() + (size_t)(c - c0) * bytes;
