@@ -73,7 +73,7 @@ struct pf_batch {
     std::vector<size_t> slot_bytes;  // bytes of every filter's workspace share
     std::vector<StepArgs> args_host; // host copy of the filters' StepArgs
     uint8_t* h_stage[kRing];
-    uint8_t* h_graph;                 // staging read by the copies of a captured step
+    uint8_t* h_graph;                 // staging read by the upload of a captured step
     // the step that last used a staging buffer: its pass C stores the number
     // in `h_seen` (pinned), by when its upload has read the buffer
     uint32_t* h_seen;
@@ -1104,12 +1104,15 @@ int pf_batch_init_cap(const pf_params* ps, int32_t n, int64_t max_tiles, void* d
     }
     // (the lists start at multiples of 8 bytes)
     b->stage_bytes = sizeof(BatchEntry) * (size_t)n + 8 * (((size_t)bl.tiles + 1) & ~(size_t)1);
+    // A kernel reads the staging buffers while the host goes on, and stores the
+    // step number that the host polls: coherent by request (the default's
+    // coherence can be changed from the environment).
     hipError_t e = hipSuccess;
     for (int i = 0; i < kRing && e == hipSuccess; ++i) {
-        e = hipHostMalloc((void**)&b->h_stage[i], b->stage_bytes, hipHostMallocDefault);
+        e = hipHostMalloc((void**)&b->h_stage[i], b->stage_bytes, hipHostMallocCoherent);
     }
-    if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_graph, b->stage_bytes, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_seen, 64, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_graph, b->stage_bytes, hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&b->h_seen, 64, hipHostMallocCoherent);
     if (e == hipSuccess) *b->h_seen = 0;
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->d_args, args.data(), sizeof(StepArgs) * (size_t)n, hipMemcpyHostToDevice, b->stream);
@@ -1176,8 +1179,9 @@ int pf_batch_step(pf_batch* b, const uint8_t* const* d_frames, const int64_t* pi
 
     // Under stream capture the step is recorded, not run: its entries and tile
     // map go through the staging buffer kept for captured steps to device
-    // buffers of their own (copies that every replay repeats, leaving the
-    // eager steps' plan alone), and no host wait or event is recorded.
+    // buffers of their own (an upload that every replay repeats, leaving the
+    // eager steps' plan alone); nothing waits for a staging buffer and no step
+    // number is stored.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     hipError_t e = hipStreamIsCapturing(b->stream, &cap);
     if (e != hipSuccess) return batch_fail(b, e, "pf_batch_step");
