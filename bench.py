@@ -46,6 +46,17 @@ def pass_a_slots(dtype, radius):
     """Algorithmic pass-A slots per update at disk radius r: the radius-5
     count with its 18 + 1 disk-sum slots replaced by 2 (2r - 1) + 1."""
     return PASS_A_SLOTS[dtype] - 19 + 2 * (2 * radius - 1) + 1
+
+
+def pass_a_stream_slots(dtype):
+    """The same where pass A streams (large FP32, FP16 and BF16 filters): a
+    particle reads its disk term and weight from the workgroup's table of pixel
+    cells (its index, the test that it is in the table: 5) instead of summing
+    its disk (19 at radius 5) and forming its weight (5).  At 2^24 FP16
+    particles, r = 8, 111.7 slots are issued (counters)."""
+    return PASS_A_SLOTS[dtype] - 19 - 5 + 5
+
+
 # Algorithmic bytes per update (spill-free): the particle's state read and
 # its resampled state written, two coordinates of 8 / 4 / 2 / 2 bytes each way.
 STATE_BYTES = {"f64": 32, "f32": 16, "f16": 8, "bf16": 8}
@@ -636,11 +647,14 @@ def run_large(pf, torch, pfsynth, args, modes):
         secs, _ = run_mode(pf, torch, fl, vl.centres, wl, dt, ls, lw, profile=False)
         _, prof = run_mode(pf, torch, fl, vl.centres, wl, dt, ls, lw, profile=True)
         a_us = 1e3 * prof[0] / prof[3]
+        # (from 2^23 particles on, at the workloads' deviations, every mode but FP64)
+        streams = dt != "f64" and wl.n_particles >= 1 << 23
+        slots = pass_a_stream_slots(dt) if streams else pass_a_slots(dt, wl.radius)
         lres[dt] = dict(ms_per_step=1e3 * secs / ls, updates_per_s=wl.n_particles * ls / secs,
                         step_roofline_frac=step_bound_s(dt, wl.radius, wl.n_particles) / (secs / ls),
                         pass_a_us=a_us, combine_us=1e3 * prof[1] / prof[3],
                         pass_c_us=1e3 * prof[2] / prof[3],
-                        pass_a_roofline_frac=pass_a_slots(dt, wl.radius) * wl.n_particles
+                        pass_a_roofline_frac=slots * wl.n_particles
                         / (a_us * 1e-6) / PEAK_LANE_OPS)
     if not args.no_track and "f64" in modes:
         ref = track(pf, fl, vl.centres, wl, "f64", wl.frames - 1)

@@ -311,7 +311,8 @@ const char* pf_last_error(void);
  * creates the events for up to `max_steps` steps (host-side objects, no device
  * memory); the following pf_step calls launch their kernels with start and
  * stop events stamped by each kernel's own dispatch (its execution time, no
- * extra queue packets); pf_profile_read waits for the stream and returns the
+ * extra queue packets; a filter of one tile, whose step is a single launch
+ * otherwise, runs the separate kernels while it is profiled); pf_profile_read waits for the stream and returns the
  * summed durations in milliseconds: out_ms[0] = pass A (propagate, likelihood, tile
  * maximum, weights, tile prefix sums), out_ms[1] = combine (global maximum,
  * normaliser, carried offsets, estimate, resampling offset), out_ms[2] = pass C

@@ -1294,7 +1294,6 @@ __device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const u
             c.W = aq->W; c.H = aq->H; c.r = aq->r; c.nd = aq->nd; c.fg = aq->fg; c.bg = aq->bg;
             c.beta = aq->beta;
             const int r = RC > 0 ? RC : c.r;
-            const bool later = t + 1 < t1;  // the table is for later tiles too
             if (tile_max == INT32_MAX) {
                 // Cells are clamped where that changes none of the disk's pixels.
                 const int lox = -(r - 1) - cnx, hix = c.W - 1 + (r - 1) - cnx;
@@ -1345,7 +1344,7 @@ __device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const u
                 };
                 bool table = false;
                 if (builds < kMaxTableBuilds) {
-                    const int m = later ? 2 : 0;
+                    const int m = t + 1 < t1 ? 2 : 0;
                     table = bw > 0 && frame_box(m, true);
                     for (int k = m; !table && k >= 0; --k) table = frame_box(k, false);
                 }
@@ -1413,7 +1412,7 @@ __device__ __forceinline__ void pass_a_stream(const cst_t<StepArgs>* ap, const u
 #pragma unroll
             for (int i = 0; i < PPT; ++i) w[i] = k0 + i < n ? weight_of(S[i], tile_max, c.beta) : (float)0;
             publish(w, tile_max);
-            if (later && bw > 0 && tile_max > ref) {
+            if (t + 1 < t1 && bw > 0 && tile_max > ref) {
                 // the table's weights, relative to the largest maximum so far
                 // (which later tiles most likely reach too)
                 ref = tile_max;
@@ -3031,20 +3030,26 @@ __device__ __forceinline__ bool rejection_accepts(const StepArgs& a, double M, i
         return ((float)(wu >> 8) + 0.5f) * 0x1.0p-24f <= __builtin_amdgcn_exp2f((float)(Sc - Smax) * a.beta);
 }
 
-// Whether the chance of a trial, the mean weight relative to the maximum, is at
-// least p (NaN: yes).
+// The normaliser Z relative to the maximum weight; Z / N is the chance of a trial.
 template <int DT>
-__device__ __forceinline__ bool rejection_chance(const StepArgs& a, float p)
+__device__ __forceinline__ auto rejection_z(const StepArgs& a)
 {
-    if constexpr (DT == PF_F64) return !(a.blk->Z < (double)p * (double)a.n);
-    else return !(a.blk->Zf < p * (float)a.n);
+    if constexpr (DT == PF_F64) return gbl(a.blk)->Z;
+    else return gbl(a.blk)->Zf;
+}
+
+// Whether that chance is at least p (NaN: yes).
+template <typename Z>
+__device__ __forceinline__ bool chance_at_least(Z z, float p, int64_t n)
+{
+    return !(z < (Z)p * (Z)n);
 }
 
 // The marks go where the prefix sums were (nothing reads them).
 template <int DT>
 __global__ __launch_bounds__(kBlock) void rejection_mask_kernel(StepArgs a)
 {
-    if (a.n > kMaskParticles && rejection_chance<DT>(a, kLikely)) return;  // they will not be read
+    if (a.n > kMaskParticles && chance_at_least(rejection_z<DT>(a), kLikely, a.n)) return;  // they will not be read
     const int j = blockIdx.x * kBlock + threadIdx.x;
     const bool mark = j < (int)a.n && rejection_accepts<DT>(a, a.blk->M, a.blk->Smax, a.s_all[min(j, (int)a.n - 1)], 0u);
     const uint64_t b = __ballot(mark);
@@ -3064,6 +3069,7 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
     const uint32_t t = blk->t;  // this step's index (the combine has advanced the count)
     const double M = blk->M;
     const int Smax = blk->Smax;
+    const auto Z = rejection_z<DT>(a);
     const auto* q_marks = gbl(static_cast<const uint32_t*>(a.q));
     // Few marks are copied to LDS at once, while the first trials' loads are in
     // flight; more, when they are known to be wanted.
@@ -3121,14 +3127,14 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
         }
         m = cap;
     };
-    if (rejection_chance<DT>(a, kLikely)) {  // the same for all
+    if (__builtin_expect(chance_at_least(Z, kLikely, n), 0)) {  // the same for all
         in_turn();
     } else if (LDS && !early) {
         copy_marks();
     }
     if (early) __syncthreads();
     const float crowd_chance = LDS || (DT == PF_F64 && n < 2 * kMaskParticles) ? 0.05f : 0.02f;
-    const bool may_crowd = crowds && rejection_chance<DT>(a, crowd_chance);
+    const bool may_crowd = crowds && chance_at_least(Z, crowd_chance, n);
     while (m < cap && __popcll(__ballot(!done)) > kFewSlots) {  // the same for the wave
         bool crowded = false;
         if (!done) {
@@ -3168,7 +3174,7 @@ __global__ __launch_bounds__(TB) void rejection_kernel(StepArgs a)
         }
         m += kTrials;
         // marks that keep little from being gathered cost more than that
-        if (may_crowd && __popcll(__ballot(crowded)) > kFewSlots / 2) in_turn();
+        if (__builtin_expect(may_crowd && __popcll(__ballot(crowded)) > kFewSlots / 2, 0)) in_turn();
     }
     for (uint64_t left = m < cap ? __ballot(!done) : 0; left; left &= left - 1) {
         const int src = __builtin_ctzll(left);

@@ -88,3 +88,11 @@ def test_what_never_streams(rule):
         for r in (1, 5, 8, 32):
             t = rule.single(0, 0, 0, r, FALL, *sigma)
             assert 4096 <= t <= never
+
+
+def test_the_bench_counts_the_pass_that_runs(rule):
+    import bench
+    for f32, dt in ((0, "f16"), (0, "bf16"), (1, "f32")):
+        assert rule.single(f32, 0, 0, 8, FALL, 5.0, 2.0) <= (1 << 23) // 1024
+        # no more than what the counters show issued, and less than with a sum per particle
+        assert bench.pass_a_stream_slots(dt) < 111.7 < bench.pass_a_slots(dt, 8)
