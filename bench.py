@@ -86,7 +86,8 @@ def step_bound_s(dtype, radius, n):
 
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "step_traffic_f16_disk1024_n1m.md")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2308_00763_amd", "csrc", f)
-                  for f in ("kernels.hip", "philox.hpp", "wave.hpp", "pf_internal.hpp")]
+                  for f in ("kernels.hip", "philox.hpp", "exp64.hpp", "wave.hpp", "pf_internal.hpp",
+                            "stream_rule.hpp")]
 
 
 def kernel_source_hash():

@@ -20,8 +20,8 @@
 //            (the same work whatever the weights), and the gather of the
 //            ancestors' propagated positions.
 //
-// From 4096 tiles on (32- and 16-bit modes, a filter's or a batch's) pass A's
-// workgroups each take a run of tiles; a single filter of one tile takes its
+// In large filters and batches of the 32- and 16-bit modes pass A's workgroups
+// each take a run of tiles (stream_rule.hpp); a single filter of one tile takes its
 // whole step in one launch.
 //
 // The maximum and weighting are fused into pass A and the cumulative
@@ -1100,14 +1100,16 @@ __global__ __launch_bounds__(kTile / PPT) void pass_a_kernel(StepArgs a)
 // Bound: vector issue.  Per wave and tile 446 vector and 24 LDS instructions
 // against pass_a_tile's 704 and 135 (r = 8), whose LDS was busy too (82 % of the
 // cycles, 48 % conflicts; now 14 %).  2^24 FP16 particles, r = 8: 85 -> 52 us;
-// the 4096-stream 256 x 256 batch 237 -> 182 us; 27 000 FP32 tiles of 192
-// streams with mixed radii 152 -> 79 us.  Six workgroups per CU: with seven or
-// eight (a smaller table, registers spilled) it was 4-8 % slower.
+// a batch of 4096 members log-spread over 256 to 65536 particles (256 x 256
+// frames) 237 -> 182 us on frames kept in the caches, 196 on the bench's 50 frames of
+// every member's own; 27 000 FP32 tiles of 192 streams with mixed radii 152 -> 79 us.
+// Six workgroups per CU: with seven or eight (a smaller table, registers
+// spilled) it was 4-8 % slower.
 //
 // The waves' issue priority falls with their progress.  Without it the oldest
 // waves ran first: of six resident workgroups the first ended after 21 us, the
-// last, alone on its CU, after 62; 2^24 particles 60 -> 52 us, the batch 205 ->
-// 182.  More, shorter workgroups instead (two rounds of them) gave half of that.
+// last, alone on its CU, after 62; 2^24 particles 60 -> 52 us, the batch (cached
+// frames) 205 -> 182.  More, shorter workgroups instead (two rounds of them) gave half of that.
 //
 // Which filters and batches stream: stream_rule.hpp.  The double mode does not:
 // it is bound by memory, and its one-tile pass needs half the registers (2^23 + 1
@@ -2676,7 +2678,7 @@ __device__ __forceinline__ void pass_c_run(const StepArgs& a, int t, PassCLds<DT
 
 // Whether a streaming pass C ranks its waves by progress: in the 16-bit modes,
 // whose pass C is bound by vector issue as much as by memory (2^24 particles
-// 38 -> 35 us, the 4096-stream batch 144 -> 136); in FP32 and FP64, bound by
+// 38 -> 35 us, a 4096-stream batch 144 -> 134-139 by its frames); in FP32 and FP64, bound by
 // memory, it costs 1 %.
 template <int DT>
 constexpr bool kPrioC = DT == PF_F16 || DT == PF_BF16;

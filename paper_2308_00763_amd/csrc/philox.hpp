@@ -80,7 +80,9 @@ __device__ __forceinline__ double uniform53_times_2_32(uint32_t hi, uint32_t lo)
 
 // -2 ln(a) for a in [2^-53, 1].  a = 2^e m with m in [sqrt(1/2), sqrt(2)), f =
 // m - 1, s = f / (2 + f): ln m = 2 atanh(s) = f - h + s (h + R) with h = f^2 / 2
-// and R the series past 2 s, over s.
+// and R the series past 2 s, over s.  (The split at sqrt(1/2), this arrangement of
+// the sum and ln 2 in two parts are those of the published fdlibm logarithm, Sun
+// Microsystems 1993; the series' coefficients are our own.)
 __device__ __forceinline__ double minus_2_ln(double a)
 {
     const uint32_t hx = (uint32_t)__double2hiint(a);
@@ -111,7 +113,8 @@ __device__ __forceinline__ double minus_2_ln(double a)
 
 // sqrt(x) for x = 0 or x in [2^-53, 128]: reciprocal square root and three
 // Goldschmidt corrections (no scaling: the argument is far from the range's
-// ends; zero becomes 1e-150, which moves no position).
+// ends; zero becomes 1e-150, so a particle that has drawn radius 0 moves by up
+// to 1e-150 deviations instead of 0).
 __device__ __forceinline__ double sqrt_near(double x)
 {
     x = __builtin_fmax(x, 1e-300);
@@ -126,7 +129,8 @@ __device__ __forceinline__ double sqrt_near(double x)
 }
 
 // cos and sin of 2 pi u 2^-32 for u in [0, 2^32): the quadrant and the rest of
-// u are exact, so the angle is reduced before it is rounded.
+// u are exact, so the angle is reduced before it is rounded.  (The cosine's last
+// sum, with what 1 - z / 2 leaves out, is arranged as in fdlibm's cosine.)
 __device__ __forceinline__ void cos_sin_turn(double u, double& c, double& s)
 {
     const double k = __builtin_rint(u * 0x1.0p-30);  // quarter turns
